@@ -64,10 +64,10 @@ HBM_PEAK_GBS = 8000.0
 
 
 # The simulation sweeps with the realization-lane kernel when R >= 64 (one realization per lane), else with the
-# fused tile kernel; the sources each kernel is built from, for matching a committed counter summary.
+# tile kernel; the sources each kernel is built from, for matching a committed counter summary.
 SWEEP_SOURCES = {
     "k_sweep_rl": ("rl_sweep.hip", "batched.hpp", "metropolis.hpp", "philox.hpp", "philox_lane.hpp", "mpr_internal.hpp"),
-    "k_sweep_fused": ("sweep_body.hpp", "sweep.hip", "metropolis.hpp", "philox.hpp", "mpr_internal.hpp"),
+    "k_tile_sweeps": ("tiles.hip", "tiles.hpp", "metropolis.hpp", "philox.hpp", "mpr_internal.hpp"),
 }
 
 
@@ -75,10 +75,10 @@ def sweep_kernel(R: int, choice: str = "auto") -> str:
     """The kernel mpr_simulate sweeps with (at the 4096^2 workload the automatic choice is the realization-lane
     kernel exactly when R >= 64)."""
     if choice == "tiles":
-        return "k_sweep_fused"
+        return "k_tile_sweeps"
     if choice == "lanes":
         return "k_sweep_rl"
-    return "k_sweep_rl" if R >= 64 else "k_sweep_fused"
+    return "k_sweep_rl" if R >= 64 else "k_tile_sweeps"
 
 
 def hbm_profile(kernel: str) -> str:

@@ -17,6 +17,7 @@
 #include "lattice3d.hpp"
 #include "mpr_internal.hpp"
 #include "rl_start.hpp"
+#include "tiles.hpp"
 
 using mpr::Carve;
 
@@ -168,8 +169,6 @@ size_t cal_ws(Carve& c, const mpr::StatsGeom& g, CalWs* w)
     return c.used;
 }
 
-int fused_tiles(int64_t H, int64_t W, int R);
-
 bool auto_stop(int32_t stop_mode) { return stop_mode == MPR_STOP_AUTO || stop_mode == MPR_STOP_AUTO_CHAIN; }
 
 struct SimWs {
@@ -182,7 +181,8 @@ struct SimWs {
     double* e_real;     // [R]
     double* series;     // [cap + 1]
     double* hist;       // per-chain stop: every realization's energy after each sweep, [cap + 1][R]
-    float* alt;         // [R][H][W] second state buffer (fused sweep)
+    float* alt;         // [R][H][W] second state buffer (tile sweeps)
+    uint32_t* plan;     // update lists of the tiles
     mpr::TBandDir* tpd; // directional coupling: per-block table
     float* rl[2];       // [HW][Rp] state buffers of the realization-lane sweep
     uint2* cells;       // its per-row window bits
@@ -197,18 +197,20 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     x.gmean = c.take<float>(1);
     x.tp = c.take<mpr::TBand>(t_count(H, W, lb_h, lb_w, cfg));
     const int64_t R = cfg->n_real > 0 ? cfg->n_real : 1;
-    const int nt = fused_tiles(H, W, (int)R);
+    const mpr::TileGeom tg = mpr::tile_geometry(H, W, (int)R);
     const int nfull = mpr::energy_full_parts(H, W);
-    const bool rl = use_rl(H, W, cfg);
+    const bool rl = use_rl(H, W, cfg), tiles = !rl && cfg->order != MPR_ORDER_DC;
     const mpr::RlGeom rg = mpr::rl_geometry(H, W, (int)R);
-    int64_t np = nt > nfull ? nt : nfull;
-    if (rl && (int64_t)rg.nbands * rg.nseg > np) np = (int64_t)rg.nbands * rg.nseg;
+    int64_t np = nfull;
+    if (tiles) np = std::max<int64_t>(np, (int64_t)tg.ntiles * tg.depth);
+    if (rl) np = std::max<int64_t>(np, (int64_t)rg.nbands * rg.nseg);
     x.epart = c.take<long long>(np * R);
-    x.e_real = c.take<double>(R);
+    x.e_real = c.take<double>(R * (tiles ? tg.depth : 1));
     const int64_t cap = auto_stop(cfg->stop_mode) ? cfg->n_max : cfg->n_eq;
     x.series = c.take<double>((cap > 0 ? cap : 0) + 1);
     x.hist = cfg->stop_mode == MPR_STOP_AUTO_CHAIN ? c.take<double>(((cap > 0 ? cap : 0) + 1) * R) : nullptr;
-    x.alt = rl ? nullptr : c.take<float>(R * H * W);
+    x.alt = tiles ? c.take<float>(R * H * W) : nullptr;
+    x.plan = tiles ? c.take<uint32_t>(tg.plan_words) : nullptr;
     x.tpd = cfg->coupling == MPR_COUPLING_DIRECTIONAL ? c.take<mpr::TBandDir>(nblocks_of(H, W, lb_h, lb_w)) : nullptr;
     x.rl[0] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
     x.rl[1] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
@@ -328,41 +330,41 @@ mpr_status check_sim_config(const mpr_sim_config& c)
 }
 
 
-// Runs fused sweeps (one launch per sweep) alternating between two state buffers.
-struct SweepRunner {
-    mpr::SweepFusedArgs a;
+// Runs tile sweeps, several per launch, alternating between two state buffers.
+struct TileRunner {
+    mpr::TileArgs a;
+    mpr::TileGeom g;
     float* buf[2];
     int cur;
     double inv_norm;
-    long long* epart;  // [R][ntiles]
-    double* e_real;    // [R]
+    long long* epart;  // [depth][R][ntiles]
+    double* e_real;    // [depth][R]
     hipStream_t s;
 
-    SweepRunner(float* state, float* alt, const uint8_t* mask, int64_t H, int64_t W, const mpr::TBand* tp,
-                int32_t lb_h, int32_t lb_w, const mpr_sim_config& c, long long* epart_, double* e_real_,
-                hipStream_t s_)
+    TileRunner(float* state, float* alt, const uint8_t* mask, int64_t H, int64_t W, const mpr::TBand* tp,
+               int32_t lb_h, int32_t lb_w, const mpr_sim_config& c, uint32_t* plan, long long* epart_,
+               double* e_real_, hipStream_t s_)
     {
-        int ntx, nty, rchunk, nchunks;
-        const int tile_h = 32;
-        mpr::fused_geometry(H, W, c.n_real, tile_h, &ntx, &nty, &rchunk, &nchunks);
-        a.tile_h = tile_h;
+        g = mpr::tile_geometry(H, W, c.n_real);
         a.src = state;
         a.dst = alt;
         a.mask = mask;
         a.Tb = tp;
+        a.plan = plan;
         a.H = (int)H;
         a.W = (int)W;
         a.lb_h = lb_h;
         a.lb_w = lb_w;
         a.nbx = (int)((W + lb_w - 1) / lb_w);
-        a.ntx = ntx;
-        a.nty = nty;
-        a.ntiles = ntx * nty;
+        a.ntx = g.ntx;
+        a.ntiles = g.ntiles;
         a.Mw = (int)((W + 3) / 4);
         a.R = c.n_real;
-        a.rchunk = rchunk;
-        a.nchunks = nchunks;
+        a.rchunk = g.rchunk;
+        a.nchunks = g.nchunks;
+        a.ns = 1;
         a.HW = H * W;
+        a.sweep = 0u;
         a.real_offset = (uint32_t)c.real_offset;
         a.scene = c.scene_id;
         a.key0 = (uint32_t)(c.seed & 0xffffffffu);
@@ -385,30 +387,28 @@ struct SweepRunner {
 
     float* current() const { return buf[cur]; }
 
-    // one sweep k; with e_dst set, e(k) is written there
-    hipError_t run(uint32_t k, double* e_dst)
+    // the update lists; the start must be in place (the samples' angles are read from it)
+    hipError_t plan() { return mpr::launch_tile_plan(a, s); }
+
+    // sweeps k .. k + n - 1, n <= depth, in one launch; with e_dst set, their energies go to e_dst[0 .. n)
+    hipError_t run(uint32_t k, int n, double* e_dst)
     {
         a.sweep = k;
+        a.ns = n;
         a.src = buf[cur];
         a.dst = buf[cur ^ 1];
         a.e_partial = e_dst ? epart : nullptr;
-        hipError_t e = mpr::launch_sweep_fused(a, s);
+        hipError_t e = mpr::launch_tile_sweeps(a, s);
         if (e != hipSuccess) return e;
         cur ^= 1;
-        if (e_dst) e = mpr::launch_energy_reduce(epart, a.ntiles, a.R, inv_norm, e_real, e_dst, s);
+        if (e_dst) e = mpr::launch_energy_reduce_n(epart, a.ntiles, a.R, n, inv_norm, e_real, e_dst, s);
         return e;
     }
 };
 
-int fused_tiles(int64_t H, int64_t W, int R)
-{
-    int ntx, nty, rc, nc;
-    mpr::fused_geometry(H, W, R, 32, &ntx, &nty, &rc, &nc);
-    return ntx * nty;
-}
-
 struct SweepWs {
     mpr::TBand* tp;
+    uint32_t* plan;
     long long* epart;
     double* e_real;
 };
@@ -417,8 +417,10 @@ size_t sweep_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, cons
     SweepWs x;
     x.tp = c.take<mpr::TBand>(t_count(H, W, lb_h, lb_w, cfg));
     const int64_t R = cfg->n_real > 0 ? cfg->n_real : 1;
-    x.epart = c.take<long long>((int64_t)fused_tiles(H, W, (int)R) * R);
-    x.e_real = c.take<double>(R);
+    const mpr::TileGeom g = mpr::tile_geometry(H, W, (int)R);
+    x.plan = c.take<uint32_t>(g.plan_words);
+    x.epart = c.take<long long>((int64_t)g.ntiles * g.depth * R);
+    x.e_real = c.take<double>(R * g.depth);
     if (w) *w = x;
     return c.used;
 }
@@ -958,7 +960,9 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     }
 
     const bool need_energy = auto_stop(c.stop_mode) || energy_out != nullptr;
-    SweepRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.epart, w.e_real, s);
+    const bool dc = c.order == MPR_ORDER_DC;
+    TileRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.plan, w.epart, w.e_real, s);
+    if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
     if (need_energy) {
         if (rl)
@@ -968,7 +972,6 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(mpr::launch_energy_reduce(w.epart, nfull, R, runner.inv_norm, w.e_real, w.series, s));
     }
     // double checkerboard: in place in `state`, energy of the whole grid after the sweep
-    const bool dc = c.order == MPR_ORDER_DC;
     mpr::DcArgs da;
     da.state = state;
     da.mask = mask;
@@ -1022,7 +1025,9 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(mpr::launch_rl_cells(mask, H, W, w.cells, s));
     }
     const int rl_parts = rl ? ra.nbands * ra.nseg : 0;
-    auto sweep = [&](uint32_t k, bool energy) -> hipError_t {
+    // sweeps k .. k + n - 1 (n > 1 on the tile sweeps only, at most max_n)
+    const int max_n = rl || dc ? 1 : runner.g.depth;
+    auto sweep = [&](uint32_t k, int n, bool energy) -> hipError_t {
         if (rl) {
             ra.sweep = k;
             hipError_t e = mpr::launch_sweep_rl(ra, w.cells, w.tp, directional ? w.tpd : nullptr, w.rl[rl_cur],
@@ -1032,7 +1037,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
                 e = mpr::launch_energy_reduce(w.epart, rl_parts, R, runner.inv_norm, w.e_real, w.series + k, s);
             return e;
         }
-        if (!dc) return runner.run(k, energy ? w.series + k : nullptr);
+        if (!dc) return runner.run(k, n, energy ? w.series + k : nullptr);
         hipError_t e = mpr::launch_dc_sweep(da, k, s);
         if (e == hipSuccess && energy) e = mpr::launch_energy_full(state, H, W, R, c.q, c.J, w.epart, nfull, s);
         if (e == hipSuccess && energy)
@@ -1057,11 +1062,17 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(chains.start(w.hist, R, c.n_fit, s));
     }
     while (k < cap) {
-        ++k;
-        MPR_HIP(sweep((uint32_t)k, need_energy));
+        // up to the next check (the first is at n_fit + n_f) or the cap
+        int n = std::min<int>(max_n, cap - k);
+        if (auto_stop(c.stop_mode)) {
+            const int64_t first = (int64_t)c.n_fit + c.n_f;
+            n = (int)std::min<int64_t>(n, k < first ? first - k : c.n_f - (k - first) % c.n_f);
+        }
+        MPR_HIP(sweep((uint32_t)(k + 1), n, need_energy));
         if (per_chain)
-            MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)k * R, w.e_real, sizeof(double) * (size_t)R,
+            MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)(k + 1) * R, w.e_real, sizeof(double) * (size_t)R * n,
                                    hipMemcpyDeviceToDevice, s));
+        k += n;
         if (auto_stop(c.stop_mode)) {
             if (k >= c.n_fit + c.n_f && (k - c.n_fit) % c.n_f == 0) {
                 bool done = false;
@@ -1083,7 +1094,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(hipMemsetAsync(acc_out, 0, sizeof(double) * (size_t)HW, s));
     }
     for (int32_t si = 1; si <= c.n_samp; ++si) {
-        MPR_HIP(sweep((uint32_t)(k_star + si), false));
+        MPR_HIP(sweep((uint32_t)(k_star + si), 1, false));
         if (rl) MPR_HIP(mpr::launch_rl_accumulate(w.rl[rl_cur], mask, HW, R, si == 1 ? 1 : 0, acc_out, s));
         else MPR_HIP(mpr::launch_accumulate(current(), mask, HW, R, si == 1 ? 1 : 0, acc_out, s));
     }
@@ -1130,10 +1141,18 @@ mpr_status mpr_sweep(float* state, float* state_alt, const uint8_t* mask, int64_
     SweepWs w;
     sweep_ws(cv, H, W, lb_h, lb_w, cfg, &w);
     MPR_HIP(mpr::launch_tpairs(T_blocks, t_count(H, W, lb_h, lb_w, cfg), cfg->J, mpr::kDeltaE * cfg->J, w.tp, s));
-    SweepRunner runner(state, state_alt, mask, H, W, w.tp, t_lb(lb_h, *cfg), t_lb(lb_w, *cfg), *cfg, w.epart,
-                       w.e_real, s);
-    for (int32_t i = 0; i < n_sweeps; ++i)
-        MPR_HIP(runner.run((uint32_t)(k_first + i), energy_out ? energy_out + i : nullptr));
+    TileRunner runner(state, state_alt, mask, H, W, w.tp, t_lb(lb_h, *cfg), t_lb(lb_w, *cfg), *cfg, w.plan, w.epart,
+                      w.e_real, s);
+    if (n_sweeps > 0) MPR_HIP(runner.plan());
+    // launches of odd numbers of sweeps, the last of one: the buffers end up as after one launch per sweep (the last
+    // state in the one, the state before it in the other)
+    for (int32_t i = 0; i < n_sweeps;) {
+        const int left = n_sweeps - 1 - i;
+        int n = left < 1 ? 1 : std::min(left, runner.g.depth);
+        if (n % 2 == 0) --n;
+        MPR_HIP(runner.run((uint32_t)(k_first + i), n, energy_out ? energy_out + i : nullptr));
+        i += n;
+    }
     return ok();
 }
 

@@ -1,5 +1,5 @@
-// Body of the fused red/black Metropolis sweep for gfx950 (Sec. 2.2.2 single checkerboard, block temperatures),
-// shared by the single-scene kernel (sweep.hip) and the batched persistent kernel (batched.hip).
+// Body of the fused red/black Metropolis sweep for gfx950 (Sec. 2.2.2 single checkerboard, block temperatures) of the
+// batched persistent kernel (batched.hip).
 //
 // One call = one sweep k of one 64 x FTH tile for a chunk of realizations.  The state is double-buffered: the tile
 // reads sweep k-1 from `src` and writes sweep k to `dst`, so it may read its neighbours' cells while they are being

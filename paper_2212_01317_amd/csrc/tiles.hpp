@@ -1,0 +1,43 @@
+// Declarations of the multi-sweep tile kernel (tiles.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "mpr_internal.hpp"
+
+namespace mpr {
+
+// A launch advances every realization by up to `depth` sweeps.
+struct TileGeom {
+    int depth;
+    int ntx, nty, ntiles;
+    int rchunk, nchunks;       // realizations per workgroup
+    size_t plan_words;         // 32-bit words of the plan (update lists of every tile)
+};
+TileGeom tile_geometry(int64_t H, int64_t W, int R);
+
+struct TileArgs {
+    const float* src;          // [R][H][W] state after sweep `sweep` - 1
+    float* dst;                // [R][H][W] state after the last sweep of the launch (samples already in place)
+    const uint8_t* mask;
+    const TBand* Tb;           // temperatures with the lb_h x lb_w layout (1 x 1: one per site)
+    uint32_t* plan;
+    int H, W, lb_h, lb_w, nbx, ntx, ntiles, Mw, R, rchunk, nchunks;
+    int ns;                    // sweeps of this launch, 1 .. depth
+    int64_t HW;
+    uint32_t sweep;            // the first sweep's index
+    uint32_t real_offset, scene, key0, key1;
+    float q, J, delta_e;
+    double two_pi_q, Jd;
+    long long* e_partial;      // [ns][R][ntiles] energy of each tile's colour-1 bonds (fixed point), or null
+};
+// the plan of a call, from its mask and the sample angles of a.src (realization 0)
+hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s);
+// a.ns sweeps, src -> dst
+hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s);
+// e_real[i][r] and e_out[i] (mean over the realizations in order) of ns sweeps, from partial [ns][R][nparts]
+hipError_t launch_energy_reduce_n(const long long* partial, int nparts, int R, int ns, double inv_norm, double* e_real,
+                                  double* e_out, hipStream_t s);
+
+}  // namespace mpr
