@@ -1821,12 +1821,12 @@ Geom3 geom3(int64_t D, int64_t H, int64_t W, int32_t lb_d, int32_t lb_h, int32_t
 {
     Geom3 g;
     g.nbands = (int)((W + mpr::kB3 - 1) / mpr::kB3);
-    g.zseg = mpr::kZSeg3;
+    g.zseg = mpr::lat3_zseg(D, H, W, R);
     g.nzseg = (int)((D + g.zseg - 1) / g.zseg);
     g.Rp = (R + 63) / 64 * 64;
     g.n_all = D * H * W;
     g.B = mpr::lat3_blocks(D, H, W, lb_d, lb_h, lb_w);
-    g.nparts = (int)(H * g.nbands * g.nzseg);
+    g.nparts = (int)((H + 1) / 2 * g.nbands * g.nzseg);
     return g;
 }
 size_t sim3_ws(Carve& c, int64_t D, int64_t H, int64_t W, int32_t lb_d, int32_t lb_h, int32_t lb_w,
@@ -1839,7 +1839,8 @@ size_t sim3_ws(Carve& c, int64_t D, int64_t H, int64_t W, int32_t lb_d, int32_t 
     x.gmean = c.take<float>(1);
     x.tp = c.take<mpr::TBand>(g.B);
     x.cells = c.take<uint32_t>(D * H * g.nbands);
-    x.lanes = c.take<float>((int64_t)g.Rp * g.n_all);
+    x.lanes = c.take<float>((int64_t)g.Rp * g.n_all + 2 * mpr::kMargin3);
+    if (x.lanes) x.lanes += mpr::kMargin3;
     const int64_t np = std::max<int64_t>(g.nparts, mpr::energy3_parts(D, H, W));
     x.epart = c.take<long long>(np * R);
     x.e_real = c.take<double>(R);
@@ -2042,8 +2043,8 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
     a.delta_e = mpr::kDeltaE3 * c.J;
     a.two_pi_q = 2.0 * mpr::kPi * (double)c.q;
     a.Jd = (double)c.J;
-    // one sweep: colour 0, then colour 1, each one launch over all rows (row tiles of kNW3 rows)
-    a.nrows = (int)((H + mpr::kNW3 - 1) / mpr::kNW3);
+    // one sweep: colour 0, then colour 1, each one launch over all row pairs
+    a.nrows = (int)((H + 1) / 2);
     auto sweep = [&](uint32_t k, bool energy) -> hipError_t {
         a.sweep = k;
         for (int colour = 0; colour < 2; ++colour) {

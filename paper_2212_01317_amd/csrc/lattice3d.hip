@@ -6,12 +6,29 @@
 // The sweep keeps the realization-lane layout of the plane, S[g][n][64] with n = (z H + y) W + x, but is a pair of
 // half-sweeps (one launch per colour): a colour-c half-sweep reads only colour-(1 - c) neighbours, which it does not
 // change, so it runs in place, with no ring of redundant updates and no second buffer, and a rejected proposal
-// writes nothing.  A wave owns kB3 columns [x0, x0 + kB3) of one row y and a segment of planes [zs, ze) of one group
-// of 64 realizations, and streams along z with a window of four planes of its row in registers ((cos, sin) of
-// columns x0 - 1 .. x0 + kB3), plus the rows y - 1 and y + 1 of the current plane at the updated columns; every row
-// is requested two steps (rows y +- 1 one step) before it is used.  The colour-c columns of a plane alternate with
-// z; for them to be known at compile time the launch takes the rows of one parity, so (y + c) mod 2 is a template
-// argument: a sweep is four launches (colours 0, 1 times row parities).
+// writes nothing.  A wave owns the columns [x0, x0 + 8) of two rows y0, y0 + 1 (y0 even) and a segment of planes of
+// one group of 64 realizations, and streams along z on its own: no barrier and no exchange with other waves.
+//
+// What a plane needs: the (cos, sin) of the other colour's cells of the two rows, five a row with the one beside the
+// band (they are also the neighbours along z of the next and the previous plane's updates, and of each other's row, so
+// each is computed once), and for the cells that are updated the angles of the cell itself and of the one neighbour
+// outside the two rows, whose (cos, sin) are taken at the update, for gap cells only.  With y0 even the updated
+// columns depend on the plane and the launch's colour alone, so the loop has one form, four planes long.
+//
+// The exact decisions wait until the wave's streaming is over: the neighbours of an undecided site do not change in this
+// half-sweep and the site keeps its angle, so only its place and the lanes in question are noted (in LDS, and the
+// streaming pauses to settle them if they become many).  Settling them on the spot is a function call with the whole
+// window live across it, for which the call's convention costs a second register for most of them.
+//
+// Measured (160^3, p = 0.6, R = 128; a sweep with its energy): 2.64 ms with four waves sharing rows through LDS behind a
+// barrier per plane and the exact test called on the spot, 1.46 ms with this layout at two waves per SIMD, 1.30 ms at
+// three and without the loads of sample cells that nothing reads (256^3, R = 64: 5.26 / 2.90 / 2.70 ms).  Bounds: at two waves
+// per SIMD a colour-0 half-sweep read 2.45 GB (the state is 2.1 GB) in 0.67 ms, near what a copy reaches, with the VALU
+// busy 59 % of the time.
+//
+// Every load of a step is issued a step ahead, and the new angles of a plane are stored a step late, right after the
+// next loads have arrived: the arrival's wait (the counter retires in order) then finds stores a step old instead of
+// ones just issued.
 //
 // The update (independent uniform proposal, FP32 filter with its error band, exact FP64 decision inside the band,
 // in the oracle's neighbour order back, up, left, right, down, front) and the fixed-point energy of the colour-1
@@ -28,9 +45,8 @@ namespace mpr {
 namespace {
 
 constexpr int kW3 = kB3 + 2;        // window columns x0 - 1 .. x0 + kB3
-constexpr int kH3 = kB3 / 2;        // updated columns of a plane (one colour)
-static_assert(kB3 % 4 == 0, "a band starts on a multiple of 4 columns (whole Philox pairs)");
-static_assert(kZSeg3 % 4 == 0, "plane segments start on a multiple of 4 planes (window slot = plane & 3)");
+constexpr uint32_t kQueue3 = 64;   // undecided updates a wave notes; four planes add at most 32
+static_assert(kB3 == 8, "two Philox pairs a row and plane");
 
 __device__ __forceinline__ int fix24(float x) { return __float2int_rn(x * 16777216.0f); }
 
@@ -76,202 +92,197 @@ __device__ __noinline__ bool exact64_6(float tp, float to, float nb, float nu, f
     return dE <= 0.0;
 }
 
-// The exact decision of the update at byte offset `off` (the lane's element of site (x, y, z)): the site's old angle
-// and its neighbours' angles from the state (the neighbours have colour 1 - c and do not change during this
-// half-sweep; the site is written only after its decision); an absent neighbour reads the site itself and is
-// excluded.
-__device__ __noinline__ bool exact3_site(const char* base, int64_t off, int64_t wrow, int64_t wplane, int x, int y,
-                                         int z, int D, int H, int W, float tp, float ui, double two_pi_q, double J,
-                                         float T)
+// philox_site with the round keys formed on the scalar unit: the sixteen key registers of RoundKeys are what keeps
+// this kernel from a third wave per SIMD.
+__device__ __forceinline__ U4 philox_site_s(uint32_t site, uint32_t w3k1, const PhiloxLane& L, uint32_t k0, uint32_t k1)
 {
-    const bool pb = z > 0, pu = y > 0, pl = x > 0, pr = x + 1 < W, pd = y + 1 < H, pf = z + 1 < D;
-    const char* p = base + off;
-    const float to = *reinterpret_cast<const float*>(p);     // the site's current angle (written only after this)
-    const float nb = *reinterpret_cast<const float*>(p + (pb ? -wplane : 0));
-    const float nu = *reinterpret_cast<const float*>(p + (pu ? -wrow : 0));
-    const float nl = *reinterpret_cast<const float*>(p + (pl ? -256 : 0));
-    const float nr = *reinterpret_cast<const float*>(p + (pr ? 256 : 0));
-    const float nd = *reinterpret_cast<const float*>(p + (pd ? wrow : 0));
-    const float nf = *reinterpret_cast<const float*>(p + (pf ? wplane : 0));
-    const unsigned present = (pb ? 1u : 0u) | (pu ? 2u : 0u) | (pl ? 4u : 0u) | (pr ? 8u : 0u) | (pd ? 16u : 0u) |
-                             (pf ? 32u : 0u);
-    return exact64_6(tp, to, nb, nu, nl, nr, nd, nf, present, two_pi_q, J, T, ui * 5.9604644775390625e-8f);
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)site;
+    const uint32_t n2u = (uint32_t)(p0 >> 32) ^ w3k1, c3u = (uint32_t)p0;
+    const uint64_t q1 = (uint64_t)0xCD9E8D57u * (uint64_t)n2u;
+    uint32_t c0 = (uint32_t)(q1 >> 32) ^ L.lc1;
+    uint32_t c1 = (uint32_t)q1;
+    uint32_t c2 = c3u ^ L.lph;
+    uint32_t c3 = L.lpl;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+#pragma unroll
+    for (int round = 2; round < 10; ++round) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const uint64_t a0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
+        const uint64_t a1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
+        const uint32_t n0 = xor3((uint32_t)(a1 >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(a0 >> 32), c3, k1);
+        c1 = (uint32_t)a1;
+        c3 = (uint32_t)a0;
+        c0 = n0;
+        c2 = n2;
+    }
+    return U4{c0, c1, c2, c3};
 }
 
-// One wave of a workgroup of kNW3 waves that own the consecutive rows y0 .. y0 + kNW3 - 1 (wave w: row y0 + w) of
-// one band, plane segment and group of realizations.  Rows y +- 1 of the current plane, at the columns the wave
-// updates, are those rows' colour-(1 - c) cells, which this half-sweep does not change: each wave publishes its own
-// row's colour-(1 - c) (cos, sin) of the next plane in LDS, and the first and last waves also load and publish the
-// rows just outside the tile (y0 - 1, y0 + kNW3).  LDS exchange: xch[buffer = plane & 1][slot][k][lane] of
-// (cos, sin), slot 0 = row y0 - 1, slot w + 1 = row y0 + w, slot kNW3 + 1 = row y0 + kNW3; k indexes the four
-// columns x0 + 2k + PX of the row below or above, whose PX is the reader's.  A wave's column parity PX = (x + y + z
-// + c) mod 2 relative to x0 depends on YC = (y + c) mod 2, a template argument of its methods; the two forms are
-// dispatched per wave and per step.
-// The launch arguments the plane loop reads (the others are used before the loop only), so that the loop keeps no
-// more scalar registers than it needs: the exact decision's FP64 constants are recomputed from q and J there as
-// the host computes them (2 pi q and J as doubles), the FP32 tolerance of T = 0 is kDeltaE3 J as on the host, the
-// temperature block row is advanced plane by plane instead of divided, and the counter word of the sweep's colour
-// is formed once.
-struct Lat3Loop {
-    int D, H, W, nbands, Mw, lb_w, lb_d;
-    uint32_t lbw_inv, w3k1;
+// What the streaming reads of the launch arguments; settling reads the others again from the argument segment, so that
+// they hold no scalar registers (and no lanes of spill registers) meanwhile.
+struct Loop3 {
+    int D, lb_d;
+    uint32_t key0, key1;
     float q, J, delta_e;
-    int64_t bz_stride;                 // temperature blocks per block plane: nby nbx
+    // one temperature column per site (AL == false) only
+    int W, lb_w;
+    uint32_t lbw_inv;
 };
 
-template <bool ENERGY>
+// C: the launch's colour.  AL: one temperature column per band (blocks a multiple of 8 wide, or one block).
+// With P = (z + C) & 1 the updated columns are x0 + 2k + P in row 0 (y0) and x0 + 2k + 1 - P in row 1 (y0 + 1),
+// k = 0 .. 3; the other colour's cells o[row][i], i = 0 .. 4, are at x0 + P - 1 + 2i and x0 - P + 2i.
+template <int C, bool ENERGY, bool AL>
 struct Wave3 {
-    Lat3Loop a;
-    const uint32_t* cells;             // [(D H) nbands] gap bits of the window columns of each row
-    const TBand* tb;
+    Loop3 a;
     char* S;                           // this wave's group of realizations
-    float2* xch;                       // LDS exchange of the workgroup
-    int y, band, x0, zs, ze, wslot;
-    uint32_t lane4, lane, real;
+    int x0, y0, zs, ze;
+    uint32_t lane4, real, w3k1;
     PhiloxLane pl;
-    RoundKeys rk;
-    int64_t wrow, wplane;              // bytes per grid row and per plane
-    int64_t orow;                      // byte offset of (plane 0, row y, window column 0) in the group
-    int64_t hoff;                      // byte offset of the halo row from row y (0: this wave loads no halo row)
-    int hslot;                         // its exchange slot
+    int64_t oz, wplane;                // byte offset of (current plane, row y0, column x0) in the group; bytes per plane
+    int d1, dU, dD;                    // byte offsets of rows y0 + 1, y0 - 1, y0 + 2 from row y0 (0: absent)
+    uint32_t site, site1, siteP;       // stream counter of the current plane's row y0; to row y0 + 1, to the next plane
+    const uint32_t* cells;             // gap bits of the current plane's row y0; words to row y0 + 1, to the next plane
+    uint32_t cell1, cellP;
+    const TBand *t0, *t1;              // temperatures of the two rows in the current block plane (AL: of the band)
+    int64_t tP;                        // temperatures per block plane
     uint32_t colmask;                  // window columns inside the grid
-    int bzc, bzr;                      // temperature block plane of the current plane, and the plane's place in it
-    int64_t byx;                       // (y / lb_h) nbx: the row's offset inside a block plane
-    float c[4][kW3], s[4][kW3];        // row y of four planes by slot (plane & 3)
-    float ang[4][kW3];                 // the same as loaded (live from the request to the arrival only)
-    uint32_t gap[4];                   // gap bits of row y of the slot's plane
-    uint32_t ngap;                     // gap bits of the plane last requested
-    float ah[kH3];                     // the halo row of the plane last requested, at the halo columns
-    float cu[kH3], su[kH3], cd[kH3], sd[kH3];   // rows y - 1 and y + 1 of the current plane at its updated columns
+    int bzr;                           // the current plane's place in its temperature block
+    uint4* queue;                      // LDS [kQueue3]: undecided updates (plane, row and cell, lanes)
+    uint32_t nq;                       // their number
+    TBand T0, T1;                      // AL: the two rows' temperatures
+    float c[4][2][5], s[4][2][5];      // (cos, sin) of the other colour's cells by slot (plane & 3)
+    float oa[2][5];                    // their angles as loaded, until they arrive
+    float own[2][2][4], out[2][2][4];  // by plane parity: angles of the updated cells, of their outer neighbours
+    float pend[2][4];                  // new angles of the last plane (negative: rejected)
+    uint32_t pgap[2];                  // its gap bits (0: nothing pending)
+    uint32_t gap[2], ngap[2];          // gap bits of the plane to be updated next and of the one after it
     long long e_acc;
 
     __device__ __forceinline__ float ld(int64_t off, int j) const
     {
         return *reinterpret_cast<const float*>(S + off + j * 256 + lane4);
     }
-    __device__ __forceinline__ void st(int64_t off, int j, float v) const
+    template <class T>
+    static __device__ __forceinline__ const T* uniform(const T* p)
     {
-        *reinterpret_cast<float*>(S + off + j * 256 + lane4) = v;
+        const uint64_t ad = (uint64_t)p;
+        return (const T*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ad) |
+                          ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(ad >> 32)) << 32));
     }
-    __device__ __forceinline__ int64_t plane_off(int z) const { return orow + (int64_t)z * wplane; }
-    __device__ __forceinline__ float2& xe(int buf, int slot, int k) const
+    // (through the constant address space: scalar loads whatever the compiler can prove about aliasing)
+    static __device__ __forceinline__ uint32_t word(const uint32_t* p)
     {
-        return xch[((buf * (kNW3 + 2) + slot) * kH3 + k) * 64 + lane];
+        return *(const __attribute__((address_space(4))) uint32_t*)uniform(p);
     }
 
-    // row y of plane z (inside the grid or not) into slot SL; its gap bits
-    template <int SL>
-    __device__ __forceinline__ void request(int z)
+    // the other colour's cells of the plane at byte offset o.  Columns beside the grid are read too: the buffer has a
+    // margin, and the arrival clears them.
+    template <int P>
+    __device__ __forceinline__ void request_others(int64_t o)
     {
-        if (z < 0 || z >= a.D) {
-            ngap = 0u;
+        const int64_t o1 = o + d1;
 #pragma unroll
-            for (int j = 0; j < kW3; ++j) ang[SL][j] = __builtin_nondeterministic_value(0.0f);
-            return;
-        }
-        using CU = const __attribute__((address_space(4))) uint32_t;
-        const uint64_t ad_ = (uint64_t)(cells + ((int64_t)z * a.H + y) * a.nbands + band);
-        const CU* pc = (const CU*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ad_) |
-                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(ad_ >> 32)) << 32));
-        ngap = *pc;
-        const int64_t off = plane_off(z);
-        if (colmask == (1u << kW3) - 1u) {
-#pragma unroll
-            for (int j = 0; j < kW3; ++j) ang[SL][j] = ld(off, j);
-        } else {
-#pragma unroll
-            for (int j = 0; j < kW3; ++j)
-                ang[SL][j] = ((colmask >> j) & 1u) ? ld(off, j) : __builtin_nondeterministic_value(0.0f);
+        for (int i = 0; i < 5; ++i) {
+            oa[0][i] = ld(o, P - 1 + 2 * i);
+            oa[1][i] = ld(o1, 2 * i - P);
         }
     }
 
-    // the requested row enters slot SL: (cos, sin) of the window, (0, 0) outside the grid (or for a plane outside)
-    // (the (cos, sin) of every column are computed from whatever the slot holds and then cleared where needed,
-    // behind scalar branches, so that the common case writes the slot once)
-    template <int SL>
+    // the updated cells of the plane at byte offset o and their neighbours in rows y0 - 1 and y0 + 2; without the energy
+    // those of its gap cells only (bits g0, g1), a fifth of the half-sweep's reads at 40 % samples
+    template <int B, int P>
+    __device__ __forceinline__ void request_own(int64_t o, uint32_t g0, uint32_t g1)
+    {
+        const int64_t o1 = o + d1, oU = o + dU, oD = o + dD;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j0 = 2 * k + P, j1 = 2 * k + 1 - P;
+            if (ENERGY || ((g0 >> (j0 + 1)) & 1u)) {
+                own[B][0][k] = ld(o, j0);
+                out[B][0][k] = ld(oU, j0);
+            } else {
+                own[B][0][k] = out[B][0][k] = __builtin_nondeterministic_value(0.0f);
+            }
+            if (ENERGY || ((g1 >> (j1 + 1)) & 1u)) {
+                own[B][1][k] = ld(o1, j1);
+                out[B][1][k] = ld(oD, j1);
+            } else {
+                own[B][1][k] = out[B][1][k] = __builtin_nondeterministic_value(0.0f);
+            }
+        }
+    }
+    // gap bits of the plane whose row y0 has its word at p
+    __device__ __forceinline__ void request_gaps(const uint32_t* p)
+    {
+        ngap[0] = word(p);
+        ngap[1] = d1 ? word(p + cell1) : 0u;
+    }
+
+    // the requested cells of plane z enter slot SL; (0, 0) outside the grid
+    template <int SL, int P>
     __device__ __forceinline__ void arrive(int z)
     {
-        gap[SL] = ngap;
 #pragma unroll
-        for (int j = 0; j < kW3; ++j) {
-            const float t = a.q * ang[SL][j];
-            c[SL][j] = cos_rev(t);
-            s[SL][j] = sin_rev(t);
-        }
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int i = 0; i < 5; ++i) {
+                const float t = a.q * oa[r][i];
+                c[SL][r][i] = cos_rev(t);
+                s[SL][r][i] = sin_rev(t);
+                oa[r][i] = __builtin_nondeterministic_value(0.0f);
+            }
         if (z < 0 || z >= a.D) {
 #pragma unroll
-            for (int j = 0; j < kW3; ++j) c[SL][j] = s[SL][j] = 0.0f;
-        } else if (colmask != (1u << kW3) - 1u) {
+            for (int r = 0; r < 2; ++r)
 #pragma unroll
-            for (int j = 0; j < kW3; ++j)
-                if (!((colmask >> j) & 1u)) c[SL][j] = s[SL][j] = 0.0f;
-        }
-    }
-
-    // publishes the (cos, sin) of row y of the plane in slot SL at the columns its neighbour rows update there (the
-    // columns of parity 1 - PX, PX this row's parity on that plane)
-    template <int SL, int PX>
-    __device__ __forceinline__ void publish(int buf) const
-    {
-#pragma unroll
-        for (int k = 0; k < kH3; ++k) xe(buf, wslot, k) = make_float2(c[SL][2 * k + 2 - PX], s[SL][2 * k + 2 - PX]);
-    }
-
-    // the halo row of plane z at this wave's updated columns there (parity PX)
-    template <int PX>
-    __device__ __forceinline__ void request_halo(int z)
-    {
-        if (z < 0 || z >= a.D) return;
-        const int64_t off = plane_off(z) + hoff;
-        if (colmask == (1u << kW3) - 1u) {
-#pragma unroll
-            for (int k = 0; k < kH3; ++k) ah[k] = ld(off, 2 * k + PX + 1);
+                for (int i = 0; i < 5; ++i) c[SL][r][i] = s[SL][r][i] = 0.0f;
         } else {
+            if (d1 == 0) {
 #pragma unroll
-            for (int k = 0; k < kH3; ++k)
-                ah[k] = ((colmask >> (2 * k + PX + 1)) & 1u) ? ld(off, 2 * k + PX + 1)
-                                                               : __builtin_nondeterministic_value(0.0f);
-        }
-    }
-    template <int PX>
-    __device__ __forceinline__ void arrive_halo(int z, int buf)
-    {
-        const bool inz = z >= 0 && z < a.D;
+                for (int i = 0; i < 5; ++i) c[SL][1][i] = s[SL][1][i] = 0.0f;
+            }
+            if (colmask != (1u << kW3) - 1u) {
 #pragma unroll
-        for (int k = 0; k < kH3; ++k) {
-            const float t = a.q * ah[k];
-            float cv = cos_rev(t), sv = sin_rev(t);
-            if (!inz || !((colmask >> (2 * k + PX + 1)) & 1u)) cv = sv = 0.0f;
-            xe(buf, hslot, k) = make_float2(cv, sv);
-            ah[k] = __builtin_nondeterministic_value(0.0f);
+                for (int i = 0; i < 5; ++i) {
+                    if (!((colmask >> (P + 2 * i)) & 1u)) c[SL][0][i] = s[SL][0][i] = 0.0f;
+                    if (!((colmask >> (1 - P + 2 * i)) & 1u)) c[SL][1][i] = s[SL][1][i] = 0.0f;
+                }
+            }
         }
     }
 
-    // rows y - 1 and y + 1 of the plane in buffer buf, from the exchange
-    __device__ __forceinline__ void read_nb(int buf)
+    // stores the accepted angles of the pending plane (at byte offset off), whose row-0 columns are 2k + P
+    template <int P>
+    __device__ __forceinline__ void flush(int64_t off)
     {
 #pragma unroll
-        for (int k = 0; k < kH3; ++k) {
-            const float2 u = xe(buf, wslot - 1, k), d = xe(buf, wslot + 1, k);
-            cu[k] = u.x;
-            su[k] = u.y;
-            cd[k] = d.x;
-            sd[k] = d.y;
+        for (int r = 0; r < 2; ++r) {
+            if (pgap[r] == 0u) continue;
+            const int64_t o = off + (r ? d1 : 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int j = 2 * k + (r ? 1 - P : P);
+                if (((pgap[r] >> (j + 1)) & 1u) && pend[r][k] >= 0.0f)
+                    *reinterpret_cast<float*>(S + o + j * 256 + lane4) = pend[r][k];
+            }
+            pgap[r] = 0u;
         }
+#pragma unroll
+        for (int r = 0; r < 2; ++r)               // dead until the next plane writes them
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pend[r][k] = __builtin_nondeterministic_value(0.0f);
     }
 
-    // temperature entry of window column j in the block row `brow` (scalar load through the constant space); xb is
-    // the band origin passed through an opaque copy, so that the column's block is computed here and not kept for
-    // every column across the plane loop
-    __device__ __forceinline__ TBand tband(int64_t brow, int xb, int j) const
+    // a temperature entry (scalar load through the constant space)
+    static __device__ __forceinline__ TBand entry(const TBand* e)
     {
-        using CU = const __attribute__((address_space(4))) uint32_t;
-        const int xr = xb - 1 + j;
-        const int x = xr < a.W ? xr : a.W - 1;     // a pair's second column may lie past the grid (not updated)
-        const int bx = a.lb_w == 1 ? x : (int)__umulhi((uint32_t)x, a.lbw_inv);
-        const uint64_t ad_ = (uint64_t)(tb + brow + bx);
-        const CU* p = (const CU*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ad_) |
-                                  ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(ad_ >> 32)) << 32));
+        const __attribute__((address_space(4))) uint32_t* p =
+            (const __attribute__((address_space(4))) uint32_t*)uniform(e);
         uint32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = p[i];
@@ -279,239 +290,277 @@ struct Wave3 {
         __builtin_memcpy(&t, w, sizeof(TBand));
         return t;
     }
-
-    // one Metropolis update of window column j of plane z (slot S0; back SP, front SN; rows y -+ 1 at index k)
-    template <int S0, int SP, int SN>
-    __device__ __forceinline__ int update(const TBand& T, int z, int64_t off, int j, int k, uint32_t wp, uint32_t wa)
+    __device__ __forceinline__ int block_column(int x) const
     {
-        const float Cx = ((((c[SP][j] + cu[k]) + c[S0][j - 1]) + c[S0][j + 1]) + cd[k]) + c[SN][j];
-        const float Sy = ((((s[SP][j] + su[k]) + s[S0][j - 1]) + s[S0][j + 1]) + sd[k]) + s[SN][j];
+        const int xc = x < a.W ? x : a.W - 1;       // a pair's second column may lie past the grid (not updated)
+        return a.lb_w == 1 ? xc : (int)__umulhi((uint32_t)xc, a.lbw_inv);
+    }
+    __device__ __forceinline__ void load_temperatures()
+    {
+        T0 = entry(t0);
+        T1 = entry(t1);
+    }
+
+    // the field of the six neighbours (back, up, left, right, down, front) of updated cell k of row R
+    template <int S0, int P, int R>
+    __device__ __forceinline__ void field(int k, float* Cx, float* Sy) const
+    {
+        constexpr int SP = (S0 + 3) & 3, SN = (S0 + 1) & 3;
+        const int iz = R == 0 ? k + P : k + 1 - P;          // the cell at the same column in the planes z -+ 1
+        float co = 0.0f, so = 0.0f;
+        if ((R == 0 ? dU : dD) != 0) {
+            const float t = a.q * out[S0 & 1][R][k];
+            co = cos_rev(t);
+            so = sin_rev(t);
+        }
+        const float cu = R == 0 ? co : c[S0][0][iz], su = R == 0 ? so : s[S0][0][iz];
+        const float cd = R == 0 ? c[S0][1][iz] : co, sd = R == 0 ? s[S0][1][iz] : so;
+        *Cx = ((((c[SP][R][iz] + cu) + c[S0][R][k]) + c[S0][R][k + 1]) + cd) + c[SN][R][iz];
+        *Sy = ((((s[SP][R][iz] + su) + s[S0][R][k]) + s[S0][R][k + 1]) + sd) + s[SN][R][iz];
+    }
+
+    // one Metropolis update of cell k of row R on plane z; returns its bonds' energy / J (fixed point) if ENERGY
+    template <int S0, int P, int R>
+    __device__ __forceinline__ int update(const TBand& T, int z, int k, uint32_t wp, uint32_t wa)
+    {
+        float Cx, Sy;
+        field<S0, P, R>(k, &Cx, &Sy);
         const float tp = u24(wp);
         const float ui = (float)(wa >> 8);
         const float angp = a.q * tp;
         const float cp = cos_rev(angp), sp = sin_rev(angp);
-        const float co = c[S0][j], so = s[S0][j];
+        const float ango = a.q * own[S0 & 1][R][k];
+        const float co = cos_rev(ango), so = sin_rev(ango);
         const float X = fmaf(cp - co, Cx, (sp - so) * Sy);
         const float w24 = exp2_fast(fminf(fmaf(X, T.kappa, 24.0f), 25.0f));
         const bool tpos = __float_as_int(T.T) > 0;
         float r = tpos ? ui - w24 : -a.J * X;
         const float tol = tpos ? fmaf(w24, fmaf(fabsf(X), T.kb, T.band), 0.015625f) : a.delta_e;
         const bool need = fabsf(r) <= tol;
-        if (__builtin_amdgcn_ballot_w64(need) != 0) {
-            int xb = x0;
-            asm volatile("" : "+s"(xb));
-            const bool ex = exact3_site(S, off + j * 256 + lane4, wrow, wplane, xb - 1 + j, y, z, a.D, a.H, a.W, tp,
-                                        ui, 2.0 * kPi * (double)a.q, (double)a.J, T.T);
-            r = need ? (ex ? -1.0f : 1.0f) : r;
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(need);
+        if (lanes != 0) {                     // undecided for now: as if rejected
+            if (lane4 == 0u)
+                queue[nq] = make_uint4((uint32_t)z, (uint32_t)(R * 4 + k), (uint32_t)lanes, (uint32_t)(lanes >> 32));
+            ++nq;
+            r = need ? 1.0f : r;
         }
         const bool acc = r < 0.0f;
-        const float cf = acc ? cp : co, sf = acc ? sp : so;
-        c[S0][j] = cf;
-        s[S0][j] = sf;
-        if (acc) st(off, j, tp);          // in place: a rejected proposal leaves the cell as it is
-        return ENERGY ? fix24(-fmaf(cf, Cx, sf * Sy)) : 0;
+        pend[R][k] = acc ? tp : -1.0f;
+        return ENERGY ? fix24(-fmaf(acc ? cp : co, Cx, (acc ? sp : so) * Sy)) : 0;
     }
 
-    // the colour of the launch on plane z (slot S0): the pairs of the updated columns, then the energy of the
-    // colour-1 sample sites
-    template <int S0, int YC>
-    __device__ __forceinline__ void plane(int z)
+    // The undecided update of queue entry i: the trial of update() from the angles in memory, decided by the exact test.
+    __device__ __forceinline__ void settle(uint32_t i, const TBand* tb)
     {
-        constexpr int SP = (S0 + 3) & 3, SN = (S0 + 1) & 3;
-        constexpr int PX = (YC + S0) & 1;              // (x + y + z + colour) even <=> x - x0 = PX mod 2
-        const int64_t off = plane_off(z);
-        const int64_t brow = (int64_t)bzc * a.bz_stride + byx;
-        const uint32_t w3k1 = a.w3k1;
-        const uint32_t base = ((uint32_t)z * (uint32_t)a.H + (uint32_t)y) * (uint32_t)a.Mw + (uint32_t)(x0 / 4);
-        int xb = x0;
-        asm volatile("" : "+s"(xb));
+        auto seg = __builtin_amdgcn_kernarg_segment_ptr();      // the launch's Lat3Args is its first argument
+        asm volatile("" : "+s"(seg));
+        const auto& A = *(const __attribute__((address_space(4))) Lat3Args*)seg;
+        const int D = A.D, H = A.H, W = A.W;
+        const int64_t wrow = (int64_t)W * 256;
+        const uint4 qe = queue[i];
+        const int z = __builtin_amdgcn_readfirstlane((int)qe.x), rk = __builtin_amdgcn_readfirstlane((int)qe.y);
+        const int R = rk >> 2, k = rk & 3, P = (z + C) & 1;
+        const int y = y0 + R, j = 2 * k + (R == 0 ? P : 1 - P), x = x0 + j;
+        const bool mine = ((lane4 < 128u ? qe.z : qe.w) >> ((lane4 >> 2) & 31u)) & 1u;
+        const bool pb = z > 0, pu = y > 0, pl_ = x > 0, pr = x + 1 < W, pd = y + 1 < H, pf = z + 1 < D;
+        char* const p = S + (((int64_t)z * H + y) * W + x) * 256 + lane4;
+        auto at = [&](int64_t off) { return *reinterpret_cast<const float*>(p + off); };
+        const float to = at(0), nb = at(pb ? -wplane : 0), nu = at(pu ? -wrow : 0), nl = at(pl_ ? -256 : 0),
+                    nr = at(pr ? 256 : 0), nd = at(pd ? wrow : 0), nf = at(pf ? wplane : 0);
+        const uint32_t pair = ((uint32_t)z * (uint32_t)H + (uint32_t)y) * (uint32_t)A.Mw + (uint32_t)(x0 / 4 + (k >> 1));
+        const U4 w = philox_site_s(pair, w3k1, pl, a.key0, a.key1);
+        const float tp = u24((k & 1) ? w.z : w.x);
+        const float u2 = u24((k & 1) ? w.w : w.y);
+        const unsigned present = (pb ? 1u : 0u) | (pu ? 2u : 0u) | (pl_ ? 4u : 0u) | (pr ? 8u : 0u) | (pd ? 16u : 0u) |
+                                 (pf ? 32u : 0u);
+        const TBand T = entry(tb + ((int64_t)(z / A.lb_d) * A.nby + y / A.lb_h) * A.nbx + x / A.lb_w);
+        const bool acc = exact64_6(tp, to, nb, nu, nl, nr, nd, nf, present, A.two_pi_q, A.Jd, T.T, u2) && mine;
+        if (acc) *reinterpret_cast<float*>(p) = tp;
+        if (ENERGY) {
+            auto cosq = [&](bool here, float t) { return here ? cos_rev(a.q * t) : 0.0f; };
+            auto sinq = [&](bool here, float t) { return here ? sin_rev(a.q * t) : 0.0f; };
+            const float Cx = ((((cosq(pb, nb) + cosq(pu, nu)) + cosq(pl_, nl)) + cosq(pr, nr)) + cosq(pd, nd)) +
+                             cosq(pf, nf);
+            const float Sy = ((((sinq(pb, nb) + sinq(pu, nu)) + sinq(pl_, nl)) + sinq(pr, nr)) + sinq(pd, nd)) +
+                             sinq(pf, nf);
+            const int before = fix24(-fmaf(cos_rev(a.q * to), Cx, sin_rev(a.q * to) * Sy));
+            const int after = fix24(-fmaf(cos_rev(a.q * tp), Cx, sin_rev(a.q * tp) * Sy));
+            if (acc) e_acc += after - before;
+        }
+    }
+
+    // the updates of row R on plane z, then the energy of the colour's sample sites
+    template <int S0, int P, int R>
+    __device__ __forceinline__ int row(int z)
+    {
+        const uint32_t g = gap[R];
+        const uint32_t base = site + (R == 0 ? 0u : site1);
         int e = 0;
 #pragma unroll
-        for (int m = 0; m < kB3 / 4; ++m) {
-            const int j0 = 4 * m + PX + 1, j1 = j0 + 2;
-            const bool g0 = (gap[S0] >> j0) & 1u, g1 = (gap[S0] >> j1) & 1u;
+        for (int m = 0; m < 2; ++m) {
+            const int j0 = 4 * m + (R == 0 ? P : 1 - P), j1 = j0 + 2;
+            const bool g0 = (g >> (j0 + 1)) & 1u, g1 = (g >> (j1 + 1)) & 1u;
             if (!(g0 || g1)) continue;
-            const TBand T0 = tband(brow, xb, j0), T1 = tband(brow, xb, j1);
-            const U4 w = philox_site(base + (uint32_t)m, w3k1, pl, rk);
-            if (g0) e += update<S0, SP, SN>(T0, z, off, j0, 2 * m, w.x, w.y);
-            if (g1) e += update<S0, SP, SN>(T1, z, off, j1, 2 * m + 1, w.z, w.w);
-        }
-        if (ENERGY) {
-            const uint32_t smp = colmask & ~gap[S0];
-#pragma unroll
-            for (int k = 0; k < kH3; ++k) {
-                const int j = 2 * k + PX + 1;
-                if (!((smp >> j) & 1u)) continue;
-                const float Cx = ((((c[SP][j] + cu[k]) + c[S0][j - 1]) + c[S0][j + 1]) + cd[k]) + c[SN][j];
-                const float Sy = ((((s[SP][j] + su[k]) + s[S0][j - 1]) + s[S0][j + 1]) + sd[k]) + s[SN][j];
-                e += fix24(-fmaf(c[S0][j], Cx, s[S0][j] * Sy));
+            TBand Ta, Tb;
+            if (AL) {
+                Ta = R == 0 ? T0 : T1;
+                Tb = Ta;
+            } else {
+                int xb = x0;
+                asm volatile("" : "+s"(xb));
+                Ta = entry((R == 0 ? t0 : t1) + block_column(xb + j0));
+                Tb = entry((R == 0 ? t0 : t1) + block_column(xb + j1));
             }
-            e_acc += e;
+            const U4 w = philox_site_s(base + (uint32_t)m, w3k1, pl, a.key0, a.key1);
+            if (g0) e += update<S0, P, R>(Ta, z, 2 * m, w.x, w.y);
+            if (g1) e += update<S0, P, R>(Tb, z, 2 * m + 1, w.z, w.w);
         }
+        if (ENERGY && (R == 0 || d1 != 0)) {
+            const uint32_t smp = colmask & ~g;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int j = 2 * k + (R == 0 ? P : 1 - P);
+                if (!((smp >> (j + 1)) & 1u)) continue;
+                float Cx, Sy;
+                field<S0, P, R>(k, &Cx, &Sy);
+                const float t = a.q * own[S0 & 1][R][k];
+                e += fix24(-fmaf(cos_rev(t), Cx, sin_rev(t) * Sy));
+            }
+        }
+        return e;
     }
 
-    // one step (S0 = z & 3): plane z + 1 arrives and is published with the halo row of plane z + 1, plane z + 2
-    // and the halo row of plane z + 2 are requested, rows y +- 1 of plane z come from the exchange, then plane z
-    // is updated.  The caller ends the step with a barrier.
-    template <int S0, int YC>
+    // one step (S0 = z & 3): plane z + 1 arrives, plane z - 1 is stored, the next loads are issued (planes past the grid
+    // are replaced by the current one; they are cleared at the arrival or never used), plane z is updated
+    template <int S0>
     __device__ __forceinline__ void step(int z)
     {
-        constexpr int SN = (S0 + 1) & 3, S2 = (S0 + 2) & 3;
-        constexpr int PX = (YC + S0) & 1, PXN = (YC + S0 + 1) & 1;
-        arrive<SN>(z + 1);
-        publish<SN, PXN>((z + 1) & 1);
-        if (hoff != 0) {
-            if (z + 1 < ze) arrive_halo<PXN>(z + 1, (z + 1) & 1);
-            if (z + 2 < ze) request_halo<PX>(z + 2);
-        }
-        if (z + 2 <= ze) request<S2>(z + 2);
-        read_nb(z & 1);
-        plane<S0, YC>(z);
+        constexpr int P = (S0 + C) & 1, SN = (S0 + 1) & 3;
+        arrive<SN, 1 - P>(z + 1);
+        flush<1 - P>(oz - wplane);
+        const uint32_t g0 = ngap[0], g1 = ngap[1];
+        const bool more = z + 1 < a.D;
+        request_others<P>(z + 2 < a.D ? oz + 2 * wplane : oz);
+        request_own<(S0 + 1) & 1, 1 - P>(more ? oz + wplane : oz, g0, g1);
+        request_gaps(z + 2 < a.D ? cells + 2 * cellP : cells);
+        int e = row<S0, P, 0>(z);
+        e += row<S0, P, 1>(z);
+        if (ENERGY) e_acc += e;
+        pgap[0] = gap[0];
+        pgap[1] = gap[1];
+        gap[0] = g0;
+        gap[1] = g1;
+        oz += wplane;
+        site += siteP;
+        cells += cellP;
         if (++bzr == a.lb_d) {
             bzr = 0;
-            ++bzc;
+            t0 += tP;
+            t1 += tP;
+            if (AL && z + 1 < ze) load_temperatures();
         }
     }
 
-    // planes zs - 1 (slot 3) and zs (slot 0) in the window and published with the halo row of plane zs, plane zs + 1
-    // and the halo row of plane zs + 1 requested; the caller then waits at the barrier
-    template <int YC>
-    __device__ __forceinline__ void start()
+    // planes [zb, ze) (zb a multiple of 4), in one stretch unless the queue fills: returns the plane reached.  oz, site,
+    // cells, t0, t1 and bzr are those of plane zb.
+    __device__ __forceinline__ int stretch(int zb)
     {
-        constexpr int PX0 = YC & 1, PX1 = (YC + 1) & 1;      // zs is a multiple of 4
-        request<3>(zs - 1);
-        arrive<3>(zs - 1);
-        request<0>(zs);
-        arrive<0>(zs);
-        publish<0, PX0>(zs & 1);
-        if (hoff != 0) {
-            request_halo<PX0>(zs);
-            arrive_halo<PX0>(zs, zs & 1);
-            if (zs + 1 < ze) request_halo<PX1>(zs + 1);
-        }
-        request<1>(zs + 1);
+        constexpr int P = C & 1;
+        nq = 0u;
+        pl = philox_lane(real, sweep_index, a.key0, a.key1);
+        pgap[0] = pgap[1] = 0u;
+        if (AL) load_temperatures();
+        request_others<1 - P>(zb > 0 ? oz - wplane : oz);
+        arrive<3, 1 - P>(zb - 1);
+        request_others<P>(oz);
+        arrive<0, P>(zb);
+        request_others<1 - P>(zb + 1 < a.D ? oz + wplane : oz);
+        request_gaps(cells);
+        gap[0] = ngap[0];
+        gap[1] = ngap[1];
+        request_own<0, P>(oz, gap[0], gap[1]);
+        request_gaps(zb + 1 < a.D ? cells + cellP : cells);
+        do {
+            step<0>(zb++);
+            if (zb < ze) step<1>(zb++);
+            if (zb < ze) step<2>(zb++);
+            if (zb < ze) step<3>(zb++);
+        } while (zb < ze && nq <= kQueue3 - 32u);
+        if ((zb - 1 + C) & 1) flush<1>(oz - wplane);     // the pending plane is zb - 1
+        else flush<0>(oz - wplane);
+        return zb;
     }
-
-    // the wave's whole segment: the start, then one step per plane, each followed by the workgroup's barrier (the
-    // exchange of plane z + 1 is complete at the barrier after step z)
-    template <int YC>
-    __device__ __forceinline__ void run()
-    {
-        start<YC>();
-        __syncthreads();
-        for (int zb = zs; zb < ze; zb += 4) {
-            step<0, YC>(zb);
-            __syncthreads();
-            if (zb + 1 >= ze) break;
-            step<1, YC>(zb + 1);
-            __syncthreads();
-            if (zb + 2 >= ze) break;
-            step<2, YC>(zb + 2);
-            __syncthreads();
-            if (zb + 3 >= ze) break;
-            step<3, YC>(zb + 3);
-            __syncthreads();
-        }
-    }
+    uint32_t sweep_index;
 };
 
-// One launch is one colour of a sweep over all rows: workgroups of kNW3 waves (consecutive rows), work items
-// (row tile, band, plane segment, group of realizations).
-template <bool ENERGY>
-__global__ __launch_bounds__(64 * kNW3) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sweep3(
+// One launch is one colour of a sweep over all rows; a workgroup is one wave, work items (band, row pair, plane segment,
+// group of realizations).
+template <int C, bool ENERGY, bool AL>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves3, kWaves3))) void k_sweep3(
     Lat3Args a, const uint32_t* __restrict__ cells, const TBand* __restrict__ tb, float* state,
     long long* __restrict__ epart)
 {
-    __shared__ float2 xch[2 * (kNW3 + 2) * kH3 * 64];
-    // XCD-aware order: workgroup g runs on XCD g % 8; consecutive items (adjacent bands) go to the same XCD.
+    // XCD-aware order: workgroup g runs on XCD g % 8; consecutive items (adjacent bands, then adjacent rows, which read
+    // each other's edge cells) go to the same XCD.
     const uint32_t N = (uint32_t)a.nrows * (uint32_t)a.nbands * (uint32_t)a.nzseg * (uint32_t)(a.Rp / 64);
     const uint32_t g = blockIdx.x, xcd = g & 7u, k = g >> 3;
     const uint32_t per = N >> 3, rem = N & 7u;
     const uint32_t item = xcd < rem ? xcd * (per + 1u) + k : rem * (per + 1u) + (xcd - rem) * per + k;
-    if (item >= N) return;                           // the whole workgroup (item is the same for its waves)
+    if (item >= N) return;
     const uint32_t band = item % (uint32_t)a.nbands;
     uint32_t rest = item / (uint32_t)a.nbands;
+    const uint32_t rows = rest % (uint32_t)a.nrows;
+    rest /= (uint32_t)a.nrows;
     const uint32_t zseg = rest % (uint32_t)a.nzseg;
-    rest /= (uint32_t)a.nzseg;
-    const uint32_t tile = rest % (uint32_t)a.nrows;
-    const uint32_t rg = rest / (uint32_t)a.nrows;
+    const uint32_t rg = rest / (uint32_t)a.nzseg;
     const int64_t n_all = (int64_t)a.D * a.H * a.W;
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    Lat3Loop la;
-    la.D = a.D;
-    la.H = a.H;
-    la.W = a.W;
-    la.nbands = a.nbands;
-    la.Mw = a.Mw;
-    la.lb_w = a.lb_w;
-    la.lb_d = a.lb_d;
-    la.lbw_inv = a.lbw_inv;
-    la.w3k1 = ctr_word3(a.scene, TAG_SWEEP, (uint32_t)a.colour) ^ a.key1;
-    la.q = a.q;
-    la.J = a.J;
-    la.delta_e = kDeltaE3 * a.J;
-    la.bz_stride = (int64_t)a.nby * a.nbx;
-    Wave3<ENERGY> w{la, cells, tb, reinterpret_cast<char*>(state) + (int64_t)rg * n_all * 256, xch};
-    const int y0 = (int)tile * kNW3;
-    w.y = y0 + wv;
-    w.band = (int)band;
+    __shared__ uint4 queue[kQueue3];
+    Wave3<C, ENERGY, AL> w;
+    w.a = Loop3{a.D, a.lb_d, a.key0, a.key1, a.q, a.J, a.delta_e, a.W, a.lb_w, a.lbw_inv};
+    w.S = reinterpret_cast<char*>(state) + (int64_t)rg * n_all * 256;
+    w.queue = queue;
     w.x0 = (int)band * kB3;
+    w.y0 = 2 * (int)rows;
     w.zs = (int)zseg * a.zseg;
     w.ze = w.zs + a.zseg < a.D ? w.zs + a.zseg : a.D;
-    w.wslot = wv + 1;
-    w.lane = threadIdx.x & 63u;
-    w.lane4 = w.lane * 4u;
-    const int lane = (int)(rg * 64 + w.lane);
+    w.lane4 = threadIdx.x * 4u;
+    const int lane = (int)(rg * 64 + threadIdx.x);
     w.real = a.real_offset + (uint32_t)lane;
-    const bool active = w.y < a.H;
-    const int yc = (w.y + a.colour) & 1;
-    // this wave's exchange slots start at zero in both buffers (rows outside the grid stay zero)
-    const float2 zero2 = make_float2(0.0f, 0.0f);
-    w.hoff = 0;
-    w.hslot = 0;
-#pragma unroll
-    for (int kk = 0; kk < kH3; ++kk) w.xe(0, w.wslot, kk) = w.xe(1, w.wslot, kk) = zero2;
-    if (wv == 0) {
-#pragma unroll
-        for (int kk = 0; kk < kH3; ++kk) w.xe(0, 0, kk) = w.xe(1, 0, kk) = zero2;
+    w.w3k1 = ctr_word3(a.scene, TAG_SWEEP, (uint32_t)C) ^ a.key1;
+    w.sweep_index = a.sweep;
+    const int wrow = a.W * 256;                       // sides up to 65535
+    const bool has1 = w.y0 + 1 < a.H;
+    w.wplane = (int64_t)a.H * wrow;
+    w.d1 = has1 ? wrow : 0;
+    w.dU = w.y0 > 0 ? -wrow : 0;
+    w.dD = w.y0 + 2 < a.H ? 2 * wrow : 0;
+    w.site1 = (uint32_t)a.Mw;
+    w.siteP = (uint32_t)a.H * (uint32_t)a.Mw;
+    w.cell1 = (uint32_t)a.nbands;
+    w.cellP = (uint32_t)a.H * (uint32_t)a.nbands;
+    w.tP = (int64_t)a.nby * a.nbx;
+    w.colmask = 0u;
+    for (int j = 0; j < kW3; ++j) {
+        const int x = w.x0 - 1 + j;
+        if (x >= 0 && x < a.W) w.colmask |= 1u << j;
     }
-    if (wv == kNW3 - 1) {
-#pragma unroll
-        for (int kk = 0; kk < kH3; ++kk) w.xe(0, kNW3 + 1, kk) = w.xe(1, kNW3 + 1, kk) = zero2;
-    }
+    w.colmask = __builtin_amdgcn_readfirstlane(w.colmask);
     w.e_acc = 0;
-    __syncthreads();                                 // the zeroed slots before any publication
-    if (active) {
-        w.pl = philox_lane(w.real, a.sweep, a.key0, a.key1);
-        w.rk = round_keys(a.key0, a.key1);
-        w.wrow = (int64_t)a.W * 256;
-        w.wplane = (int64_t)a.H * w.wrow;
-        w.orow = ((int64_t)w.y * a.W + (w.x0 - 1)) * 256;
-        w.colmask = 0u;
-        for (int j = 0; j < kW3; ++j) {
-            const int x = w.x0 - 1 + j;
-            if (x >= 0 && x < a.W) w.colmask |= 1u << j;
-        }
-        w.colmask = __builtin_amdgcn_readfirstlane(w.colmask);
-        w.bzc = w.zs / a.lb_d;
-        w.bzr = w.zs % a.lb_d;
-        w.byx = (int64_t)(w.y / a.lb_h) * a.nbx;
-        if (wv == 0 && y0 > 0) {
-            w.hoff = -w.wrow;
-            w.hslot = 0;
-        }
-        if (wv == kNW3 - 1 && y0 + kNW3 < a.H) {
-            w.hoff = w.wrow;
-            w.hslot = kNW3 + 1;
-        }
-        // every wave of the workgroup passes the same number of barriers: one after the start and one per plane
-        if (yc) w.template run<1>();
-        else w.template run<0>();
-    } else {
-        for (int z = w.zs - 1; z < w.ze; ++z) __syncthreads();
+    const int bcol = AL ? w.block_column(w.x0) : 0;
+    for (int z = w.zs; z < w.ze;) {
+        const int64_t plane = (int64_t)z * a.H + w.y0;
+        w.oz = (plane * a.W + w.x0) * 256;
+        w.site = (uint32_t)plane * (uint32_t)a.Mw + (uint32_t)(w.x0 / 4);
+        w.cells = cells + plane * a.nbands + band;
+        const int bz = z / a.lb_d;
+        w.bzr = z % a.lb_d;
+        w.t0 = tb + ((int64_t)bz * a.nby + w.y0 / a.lb_h) * a.nbx + bcol;
+        w.t1 = has1 ? tb + ((int64_t)bz * a.nby + (w.y0 + 1) / a.lb_h) * a.nbx + bcol : w.t0;
+        z = w.stretch(z);
+        for (uint32_t i = 0; i < w.nq; ++i) w.settle(i, tb);
     }
-    if (ENERGY && active && lane < a.R)
-        epart[(int64_t)lane * ((int64_t)a.H * a.nbands * a.nzseg) + ((int64_t)w.y * a.nbands + band) * a.nzseg +
+    if (ENERGY && lane < a.R)
+        epart[(int64_t)lane * ((int64_t)a.nrows * a.nbands * a.nzseg) + ((int64_t)rows * a.nbands + band) * a.nzseg +
               zseg] = w.e_acc;
 }
 
@@ -746,6 +795,17 @@ hipError_t launch_energy3_full(const float* state, int64_t D, int64_t H, int64_t
     return hipGetLastError();
 }
 
+int lat3_zseg(int64_t D, int64_t H, int64_t W, int R)
+{
+    const int64_t per = ((W + kB3 - 1) / kB3) * ((H + 1) / 2) * ((R + 63) / 64);
+    auto planes = [&](int64_t n) { return (int)(((D + n - 1) / n + 3) / 4 * 4); };
+    int64_t n = (D + kZSeg3 - 1) / kZSeg3;
+        // at least 16384 waves (3072 run at once: the last round is then a small part), but 8 planes: a segment's first
+    // two planes are loaded in vain (160^3, R = 128: 1.44 ms per sweep with 9600 waves, 1.40 with 16000)
+    while (per * n < 16384 && planes(n) > 8) ++n;
+    return planes(n);
+}
+
 hipError_t launch_cells3(const uint8_t* mask, int64_t D, int64_t H, int64_t W, int nbands, uint32_t* cells,
                          hipStream_t s)
 {
@@ -761,8 +821,20 @@ hipError_t launch_sweep3(const Lat3Args& a, const uint32_t* cells, const TBand* 
     const int64_t N = (int64_t)a.nrows * a.nbands * a.nzseg * (a.Rp / 64);
     if (N <= 0) return hipSuccess;
     const dim3 grid((unsigned)N);
-    if (epart) hipLaunchKernelGGL((k_sweep3<true>), grid, dim3(64 * kNW3), 0, s, a, cells, tb, state, epart);
-    else hipLaunchKernelGGL((k_sweep3<false>), grid, dim3(64 * kNW3), 0, s, a, cells, tb, state, epart);
+    const bool al = a.lb_w % kB3 == 0 || a.nbx == 1;
+#define MPR_S3(CO, EN, AL) \
+    hipLaunchKernelGGL((k_sweep3<CO, EN, AL>), grid, dim3(64), 0, s, a, cells, tb, state, epart)
+    if (a.colour == 0) {                         // the energy is that of the colour-1 sites
+        if (al) MPR_S3(0, false, true);
+        else MPR_S3(0, false, false);
+    } else if (epart) {
+        if (al) MPR_S3(1, true, true);
+        else MPR_S3(1, true, false);
+    } else {
+        if (al) MPR_S3(1, false, true);
+        else MPR_S3(1, false, false);
+    }
+#undef MPR_S3
     return hipGetLastError();
 }
 

@@ -14,12 +14,15 @@ namespace mpr {
 // The FP32 filter's bound on |dE_fp32 - dE_exact| / J with six neighbours: |(Cx, Sy)| <= 6 makes the terms of the
 // plane's derivation 3/2 as large, about 2.3e-5 with every FP32 rounding; 2.75e-5 leaves margin.
 constexpr float kDeltaE3 = 2.75e-5f;
-constexpr int kB3 = 8;           // owned columns of a wave of the 3D sweep (16 would need more than 256 VGPRs)
-constexpr int kZSeg3 = 64;       // planes of a wave's segment
-constexpr int kNW3 = 4;          // waves (consecutive rows) of a workgroup of the 3D sweep
+constexpr int kB3 = 8;           // columns of a wave's two rows (163 VGPRs; three waves per SIMD have 168)
+constexpr int kZSeg3 = 64;       // most planes of a wave's segment (a multiple of 4: window slot = plane & 3)
+constexpr int kWaves3 = 3;       // waves per SIMD the 3D sweep is compiled for
+constexpr int64_t kMargin3 = 1024;   // floats before and after the lane buffer that the sweep may read (and ignores)
+// planes of a segment: about equal segments of at most kZSeg3, shortened while the device has too few waves
+int lat3_zseg(int64_t D, int64_t H, int64_t W, int R);
 struct Lat3Args {
     int D, H, W, R, Rp, Mw, nbands, nzseg, zseg;
-    int nrows;                   // row tiles of kNW3 rows
+    int nrows;                   // row pairs
     int lb_d, lb_h, lb_w, nbx, nby;
     uint32_t lbw_inv;            // ceil(2^32 / lb_w) for lb_w > 1
     uint32_t sweep, real_offset, scene, key0, key1;
@@ -54,7 +57,8 @@ hipError_t launch_energy3_full(const float* state, int64_t D, int64_t H, int64_t
 hipError_t launch_cells3(const uint8_t* mask, int64_t D, int64_t H, int64_t W, int nbands, uint32_t* cells,
                          hipStream_t s);
 // one half-sweep (colour a.colour, all rows) of the lane-layout state [G][n][64], in place; with epart set, the
-// fixed-point energy of each row's colour-1 sites goes to epart[r][(y * nbands + band) * nzseg + zseg]
+// fixed-point energy of each row pair's colour-1 sites goes to epart[r][(pair * nbands + band) * nzseg + zseg]; the
+// buffer has kMargin3 floats on either side
 hipError_t launch_sweep3(const Lat3Args& a, const uint32_t* cells, const TBand* tb, float* state, long long* epart,
                          hipStream_t s);
 // the matching curve of the cubic lattice: periodic L^3, one chain per temperature
