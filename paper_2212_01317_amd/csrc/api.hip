@@ -171,6 +171,14 @@ size_t cal_ws(Carve& c, const mpr::StatsGeom& g, CalWs* w)
 
 bool auto_stop(int32_t stop_mode) { return stop_mode == MPR_STOP_AUTO || stop_mode == MPR_STOP_AUTO_CHAIN; }
 
+// Sampling sweeps that run in one launch of the tile sweeps and leave a state each for the accumulation: where the
+// states are small (their launches would cost more than the extra copy), else one sweep per launch.
+int snap_sweeps(int64_t H, int64_t W, int R, int32_t n_samp, int depth)
+{
+    const int64_t n = std::min<int64_t>(n_samp, depth);
+    return n > 1 && n * R * H * W <= ((int64_t)16 << 20) ? (int)n : 1;
+}
+
 struct SimWs {
     StatsWs st;
     double* Ts;
@@ -183,6 +191,7 @@ struct SimWs {
     double* hist;       // per-chain stop: every realization's energy after each sweep, [cap + 1][R]
     float* alt;         // [R][H][W] second state buffer (tile sweeps)
     uint32_t* plan;     // update lists of the tiles
+    float* snap;        // [snap_sweeps][R][H][W] states of the sampling sweeps of one launch
     mpr::TBandDir* tpd; // directional coupling: per-block table
     float* rl[2];       // [HW][Rp] state buffers of the realization-lane sweep
     uint2* cells;       // its per-row window bits
@@ -211,6 +220,8 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     x.hist = cfg->stop_mode == MPR_STOP_AUTO_CHAIN ? c.take<double>(((cap > 0 ? cap : 0) + 1) * R) : nullptr;
     x.alt = tiles ? c.take<float>(R * H * W) : nullptr;
     x.plan = tiles ? c.take<uint32_t>(tg.plan_words) : nullptr;
+    const int64_t ss = tiles ? snap_sweeps(H, W, (int)R, cfg->n_samp, tg.depth) : 1;
+    x.snap = ss > 1 ? c.take<float>(ss * R * H * W) : nullptr;
     x.tpd = cfg->coupling == MPR_COUPLING_DIRECTIONAL ? c.take<mpr::TBandDir>(nblocks_of(H, W, lb_h, lb_w)) : nullptr;
     x.rl[0] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
     x.rl[1] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
@@ -374,6 +385,7 @@ struct TileRunner {
         a.delta_e = mpr::kDeltaE * c.J;
         a.two_pi_q = 2.0 * mpr::kPi * (double)c.q;
         a.Jd = (double)c.J;
+        a.snap = nullptr;
         a.e_partial = nullptr;
         buf[0] = state;
         buf[1] = alt;
@@ -390,9 +402,11 @@ struct TileRunner {
     // the update lists; the start must be in place (the samples' angles are read from it)
     hipError_t plan() { return mpr::launch_tile_plan(a, s); }
 
-    // sweeps k .. k + n - 1, n <= depth, in one launch; with e_dst set, their energies go to e_dst[0 .. n)
-    hipError_t run(uint32_t k, int n, double* e_dst)
+    // sweeps k .. k + n - 1, n <= depth, in one launch; with e_dst set, their energies go to e_dst[0 .. n); with snap set
+    // (and no e_dst), their states to snap[0 .. n)
+    hipError_t run(uint32_t k, int n, double* e_dst, float* snap = nullptr)
     {
+        a.snap = snap;
         a.sweep = k;
         a.ns = n;
         a.src = buf[cur];
@@ -1093,7 +1107,15 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     if (c.n_samp == 0) {
         MPR_HIP(hipMemsetAsync(acc_out, 0, sizeof(double) * (size_t)HW, s));
     }
-    for (int32_t si = 1; si <= c.n_samp; ++si) {
+    if (w.snap) {
+        const int per = snap_sweeps(H, W, R, c.n_samp, runner.g.depth);
+        for (int32_t si = 0; si < c.n_samp; si += per) {
+            const int n = std::min<int>(per, c.n_samp - si);
+            MPR_HIP(runner.run((uint32_t)(k_star + si + 1), n, nullptr, w.snap));
+            MPR_HIP(mpr::launch_accumulate_n(w.snap, mask, HW, R, n, si == 0, acc_out, s));
+        }
+    }
+    for (int32_t si = 1; si <= (w.snap ? 0 : c.n_samp); ++si) {
         MPR_HIP(sweep((uint32_t)(k_star + si), 1, false));
         if (rl) MPR_HIP(mpr::launch_rl_accumulate(w.rl[rl_cur], mask, HW, R, si == 1 ? 1 : 0, acc_out, s));
         else MPR_HIP(mpr::launch_accumulate(current(), mask, HW, R, si == 1 ? 1 : 0, acc_out, s));

@@ -30,12 +30,16 @@ struct TileArgs {
     uint32_t real_offset, scene, key0, key1;
     float q, J, delta_e;
     double two_pi_q, Jd;
+    float* snap;               // [ns][R][H][W]: the gap cells of every sweep's state too, or null (no energies then)
     long long* e_partial;      // [ns][R][ntiles] energy of each tile's colour-1 bonds (fixed point), or null
 };
 // the plan of a call, from its mask and the sample angles of a.src (realization 0)
 hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s);
 // a.ns sweeps, src -> dst
 hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s);
+// acc[n] += the gap angles of ns states [ns][R][HW], state by state, over the realizations in order; first: from 0
+hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t HW, int R, int ns, bool first,
+                               double* acc, hipStream_t s);
 // e_real[i][r] and e_out[i] (mean over the realizations in order) of ns sweeps, from partial [ns][R][nparts]
 hipError_t launch_energy_reduce_n(const long long* partial, int nparts, int R, int ns, double inv_norm, double* e_real,
                                   double* e_out, hipStream_t s);

@@ -79,3 +79,12 @@ def test_continued_sweeps_leave_the_last_two_states_in_the_two_buffers(n):
     assert np.array_equal(host(e), np.array(energies))
     # (an odd count ends in state_alt, from which the binding copies the result back)
     assert np.array_equal(host(alt), host(one if n % 2 else two))
+
+
+@pytest.mark.parametrize("n_eq,n_samp", [(0, 2), (3, 5), (1, 6), (5, 11)])
+def test_sampling_sweeps_of_one_launch_match_oracle(n_eq, n_samp):
+    t, mask, T = _scene(45, 99, 0.5, (16, 16))
+    kw = dict(n_real=3, init_mode=0, stop_mode=0, n_eq=n_eq, n_samp=n_samp, seed=21)
+    o = oracle.simulate(t, mask, T, 16, 16, OCfg(**kw))
+    g = M.mpr_simulate(dev(t), dev(mask), dev(T), 16, 16, M.SimConfig(sweep_kernel=M.SWEEP_TILES, **kw))
+    assert np.array_equal(host(g.state), o.state) and np.array_equal(host(g.acc), o.acc)
