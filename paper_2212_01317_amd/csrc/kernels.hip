@@ -847,9 +847,109 @@ __global__ __launch_bounds__(256) void k_sst_round(const double* a, int64_t n, f
     if (i < n) out[i] = (float)a[i];
 }
 
+// The passes of radius 1 and 2 fused: a workgroup loads a 64 x 32 tile with a ring of passes x R sites, straight from the
+// block map in the first launch, runs the passes in LDS on a region that shrinks by R a pass, and writes the tile, as FP32
+// after the last pass.  A thread makes four sites of a column from one walk down the rows, so each value is read from LDS
+// once per column offset instead of once per window.  The sums keep the order of k_sst_pass (a site outside the grid
+// adds 0).  4096^2, 32 x 32 blocks, five passes of radius 1:
+// 648 us as seven kernels over two FP64 planes (0.27 GB a pass), 217 us fused (radius 2, five passes: 1222 / 335 us);
+// bound by the LDS reads and FP64 additions and the barrier of each pass (256 / 384 / 768 threads: 272 / 399 / 226 us).
+constexpr int kSstW = 64, kSstH = 32, kSstRing = 6, kSstNT = 512;
+constexpr int kSstStride = kSstW + 2 * kSstRing + 1;
+
+template <int R>
+__global__ __launch_bounds__(kSstNT) void k_sst_fused(const float* __restrict__ T_blocks,
+                                                      const double* __restrict__ in, int H, int W, int lb_h, int lb_w,
+                                                      int passes, double* __restrict__ out, float* __restrict__ out32)
+{
+    constexpr int K = 4, N1 = 2 * R + 1;
+    // (a column's last four sites may reach past the region: those rows are read and not used)
+    __shared__ double buf[2][(kSstH + 2 * kSstRing + K) * kSstStride];
+    const int ring = passes * R;
+    const int rw = kSstW + 2 * ring, rh = kSstH + 2 * ring;
+    const int ntx = (W + kSstW - 1) / kSstW;
+    const int x0 = (int)(blockIdx.x % (unsigned)ntx) * kSstW - ring, y0 = (int)(blockIdx.x / (unsigned)ntx) * kSstH - ring;
+    const int nbx = (W + lb_w - 1) / lb_w;
+    for (int i = threadIdx.x; i < rw * rh; i += kSstNT) {
+        const int ry = i / rw, rx = i - ry * rw, y = y0 + ry, x = x0 + rx;
+        double v = 0.0;
+        if (y >= 0 && y < H && x >= 0 && x < W)
+            v = in ? in[(int64_t)y * W + x] : (double)T_blocks[(int64_t)(y / lb_h) * nbx + x / lb_w];
+        buf[0][ry * kSstStride + rx] = v;
+    }
+    __syncthreads();
+    for (int p = 0; p < passes; ++p) {
+        const double* const a = buf[p & 1];
+        double* const b = buf[(p & 1) ^ 1];
+        const int lo = (p + 1) * R, pw = rw - 2 * lo, ph = rh - 2 * lo;     // the region after this pass
+        const unsigned inv = 65536u / (unsigned)pw + 1u;     // i / pw for i < 65536 / pw (at most 11 groups of columns)
+        for (int i = threadIdx.x; i < pw * ((ph + K - 1) / K); i += kSstNT) {
+            const int g = (int)(((unsigned)i * inv) >> 16), rx = lo + i - g * pw, ry = lo + g * K, x = x0 + rx;
+            double v[K + 2 * R][2 * R + 1];
+#pragma unroll
+            for (int k = 0; k < K + 2 * R; ++k)
+#pragma unroll
+                for (int d = 0; d <= 2 * R; ++d)
+                    v[k][d] = a[(ry - R + k) * kSstStride + rx - R + d];
+            const int nx = (x + R < W - 1 ? x + R : W - 1) - (x - R > 0 ? x - R : 0) + 1;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                double sum = 0.0;
+#pragma unroll
+                for (int e = 0; e <= 2 * R; ++e)
+#pragma unroll
+                    for (int d = 0; d <= 2 * R; ++d) sum += v[k + e][d];
+                const int y = y0 + ry + k;
+                const int ny = (y + R < H - 1 ? y + R : H - 1) - (y - R > 0 ? y - R : 0) + 1;
+                double m;
+                if (nx == N1 && ny == N1) {
+                    // the correctly rounded quotient: one Newton step on sum times the correctly rounded reciprocal
+                    // (an infinite or NaN sum is its own quotient)
+                    const double q = sum * (1.0 / (N1 * N1));
+                    m = fma(fma(-(double)(N1 * N1), q, sum), 1.0 / (N1 * N1), q);
+                    if (!(fabs(sum) < INFINITY)) m = sum;
+                } else {
+                    m = sum / (double)(ny * nx);
+                }
+                if (ry + k < lo + ph) b[(ry + k) * kSstStride + rx] = y >= 0 && y < H && x >= 0 && x < W ? m : 0.0;
+            }
+        }
+        __syncthreads();
+    }
+    const double* const r = buf[passes & 1];
+    for (int i = threadIdx.x; i < kSstW * kSstH; i += kSstNT) {
+        const int ry = i / kSstW, rx = i % kSstW, y = y0 + ring + ry, x = x0 + ring + rx;
+        if (y >= H || x >= W) continue;
+        const double v = r[(ring + ry) * kSstStride + ring + rx];
+        if (out32) out32[(int64_t)y * W + x] = (float)v;
+        else out[(int64_t)y * W + x] = v;
+    }
+}
+
 hipError_t launch_sst(const float* T_blocks, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, int32_t r_s,
                       int32_t n_s, double* a, double* b, float* out, hipStream_t s)
 {
+    if (n_s > 0 && (r_s == 1 || r_s == 2)) {      // wider windows: one pass per launch (their ring would outgrow the LDS)
+        const dim3 tiles((unsigned)(((W + kSstW - 1) / kSstW) * ((H + kSstH - 1) / kSstH)));
+        const double* in = nullptr;
+        for (int32_t done = 0; done < n_s;) {
+            const int p = n_s - done < kSstRing / r_s ? n_s - done : kSstRing / r_s;
+            done += p;
+            float* const o32 = done == n_s ? out : nullptr;
+            if (r_s == 1)
+                hipLaunchKernelGGL(k_sst_fused<1>, tiles, dim3(kSstNT), 0, s, T_blocks, in, (int)H, (int)W, lb_h, lb_w, p,
+                                   a, o32);
+            else
+                hipLaunchKernelGGL(k_sst_fused<2>, tiles, dim3(kSstNT), 0, s, T_blocks, in, (int)H, (int)W, lb_h, lb_w, p,
+                                   a, o32);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+            in = a;
+            a = b;
+            b = const_cast<double*>(in);
+        }
+        return hipSuccess;
+    }
     const int64_t n = H * W;
     const dim3 grid((unsigned)((n + 255) / 256));
     hipLaunchKernelGGL(k_sst_spread, grid, dim3(256), 0, s, T_blocks, H, W, lb_h, lb_w, a);
