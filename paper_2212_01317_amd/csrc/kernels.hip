@@ -53,45 +53,100 @@ int map_reduce_blocks(int64_t n)
     return (int)(b < 1 ? 1 : (b > 2048 ? 2048 : b));
 }
 
+// The maps over all sites are bound by memory.  V sites at i: four per thread and load where the number of sites and every
+// pointer allow it (4096 x 4096 sites: k_map_apply 37.5 -> 21.8 us, k_predict 79 -> 47, k_validate_part 44 -> 26), else one.
+template <int V, class T>
+__device__ __forceinline__ void load_v(const T* p, int64_t i, T* out)
+{
+    if constexpr (V == 4) {
+        typedef T vec __attribute__((ext_vector_type(4)));
+        const vec v = *reinterpret_cast<const vec*>(p + i);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) out[k] = v[k];
+    } else {
+        out[0] = p[i];
+    }
+}
+template <int V, class T>
+__device__ __forceinline__ void store_v(T* p, int64_t i, const T* in)
+{
+    if constexpr (V == 4) {
+        typedef T vec __attribute__((ext_vector_type(4)));
+        vec v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = in[k];
+        *reinterpret_cast<vec*>(p + i) = v;
+    } else {
+        p[i] = in[0];
+    }
+}
+template <class... P>
+bool aligned4(int64_t n, const P*... p)
+{
+    return n % 4 == 0 && (((uintptr_t)p % (4 * sizeof(P)) == 0) && ...);
+}
+
+// min, max, count and non-finite count over a workgroup, in thread 0
+__device__ __forceinline__ void map_reduce_group(float& mn, float& mx, unsigned long long& cnt, unsigned long long& bad)
+{
+    __shared__ float smn[MAP_NT / 64], smx[MAP_NT / 64];
+    __shared__ unsigned long long sc[MAP_NT / 64], sb[MAP_NT / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        mn = fminf(mn, __shfl_xor(mn, o, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+    }
+    cnt = wave_sum(cnt);
+    bad = wave_sum(bad);
+    const int w = (int)(threadIdx.x >> 6);
+    if ((threadIdx.x & 63u) == 0) {
+        smn[w] = mn;
+        smx[w] = mx;
+        sc[w] = cnt;
+        sb[w] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < MAP_NT / 64; ++i) {
+            mn = fminf(mn, smn[i]);
+            mx = fmaxf(mx, smx[i]);
+            cnt += sc[i];
+            bad += sb[i];
+        }
+    }
+}
+
+template <int V>
 __global__ __launch_bounds__(MAP_NT) void k_map_reduce(const float* __restrict__ z, const uint8_t* __restrict__ mask,
                                                         int64_t n, float* pmin, float* pmax, unsigned long long* pcnt,
                                                         unsigned long long* pbad)
 {
-    __shared__ float smn[MAP_NT], smx[MAP_NT];
-    __shared__ unsigned long long sc[MAP_NT], sb[MAP_NT];
     float mn = INFINITY, mx = -INFINITY;
-    unsigned long long cnt = 0, bad = 0;
-    for (int64_t i = (int64_t)blockIdx.x * MAP_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * MAP_NT) {
-        if (mask[i]) {
-            const float v = z[i];
-            if (isfinite(v)) {
-                mn = fminf(mn, v);
-                mx = fmaxf(mx, v);
+    unsigned cnt = 0, bad = 0;
+    for (int64_t i = ((int64_t)blockIdx.x * MAP_NT + threadIdx.x) * V; i < n; i += (int64_t)gridDim.x * MAP_NT * V) {
+        float zv[V];
+        uint8_t m[V];
+        load_v<V>(z, i, zv);
+        load_v<V>(mask, i, m);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            if (!m[k]) continue;
+            if (isfinite(zv[k])) {
+                mn = fminf(mn, zv[k]);
+                mx = fmaxf(mx, zv[k]);
             } else {
                 ++bad;
             }
             ++cnt;
         }
     }
-    smn[threadIdx.x] = mn;
-    smx[threadIdx.x] = mx;
-    sc[threadIdx.x] = cnt;
-    sb[threadIdx.x] = bad;
-    __syncthreads();
-    for (int s = MAP_NT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            smn[threadIdx.x] = fminf(smn[threadIdx.x], smn[threadIdx.x + s]);
-            smx[threadIdx.x] = fmaxf(smx[threadIdx.x], smx[threadIdx.x + s]);
-            sc[threadIdx.x] += sc[threadIdx.x + s];
-            sb[threadIdx.x] += sb[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
+    unsigned long long c = cnt, b = bad;
+    map_reduce_group(mn, mx, c, b);
     if (threadIdx.x == 0) {
-        pmin[blockIdx.x] = smn[0];
-        pmax[blockIdx.x] = smx[0];
-        pcnt[blockIdx.x] = sc[0];
-        pbad[blockIdx.x] = sb[0];
+        pmin[blockIdx.x] = mn;
+        pmax[blockIdx.x] = mx;
+        pcnt[blockIdx.x] = c;
+        pbad[blockIdx.x] = b;
     }
 }
 
@@ -100,8 +155,6 @@ __global__ __launch_bounds__(MAP_NT) void k_map_finalize(const float* pmin, cons
                                                           const unsigned long long* pbad, int nblocks, double* range,
                                                           unsigned long long* counts)
 {
-    __shared__ float smn[MAP_NT], smx[MAP_NT];
-    __shared__ unsigned long long sc[MAP_NT], sb[MAP_NT];
     float mn = INFINITY, mx = -INFINITY;
     unsigned long long cnt = 0, bad = 0;
     for (int i = threadIdx.x; i < nblocks; i += MAP_NT) {
@@ -110,45 +163,40 @@ __global__ __launch_bounds__(MAP_NT) void k_map_finalize(const float* pmin, cons
         cnt += pcnt[i];
         bad += pbad[i];
     }
-    smn[threadIdx.x] = mn;
-    smx[threadIdx.x] = mx;
-    sc[threadIdx.x] = cnt;
-    sb[threadIdx.x] = bad;
-    __syncthreads();
-    for (int s = MAP_NT / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            smn[threadIdx.x] = fminf(smn[threadIdx.x], smn[threadIdx.x + s]);
-            smx[threadIdx.x] = fmaxf(smx[threadIdx.x], smx[threadIdx.x + s]);
-            sc[threadIdx.x] += sc[threadIdx.x + s];
-            sb[threadIdx.x] += sb[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
+    map_reduce_group(mn, mx, cnt, bad);
     if (threadIdx.x == 0) {
-        range[0] = (double)smn[0];
-        range[1] = (double)smx[0];
-        counts[0] = sc[0];
-        counts[1] = sb[0];
+        range[0] = (double)mn;
+        range[1] = (double)mx;
+        counts[0] = cnt;
+        counts[1] = bad;
     }
 }
 
+template <int V>
 __global__ __launch_bounds__(MAP_NT) void k_map_apply(const float* __restrict__ z, const uint8_t* __restrict__ mask,
                                                        int64_t n, const double* __restrict__ range,
                                                        float* __restrict__ t)
 {
-    const int64_t i = (int64_t)blockIdx.x * MAP_NT + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * MAP_NT + threadIdx.x) * V;
     if (i >= n) return;
     const double zmin = range[0];
     const double span = range[1] - range[0];
-    float v = 0.0f;
-    if (mask[i] && span != 0.0) v = (float)(((double)z[i] - zmin) / span);
-    t[i] = v;
+    float zv[V], tv[V];
+    uint8_t m[V];
+    load_v<V>(z, i, zv);
+    load_v<V>(mask, i, m);
+#pragma unroll
+    for (int k = 0; k < V; ++k) tv[k] = m[k] && span != 0.0 ? (float)(((double)zv[k] - zmin) / span) : 0.0f;
+    store_v<V>(t, i, tv);
 }
 
 hipError_t launch_map_reduce(const float* z, const uint8_t* mask, int64_t n, float* pmin, float* pmax,
                              unsigned long long* pcnt, unsigned long long* pbad, int nblocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_map_reduce, dim3(nblocks), dim3(MAP_NT), 0, s, z, mask, n, pmin, pmax, pcnt, pbad);
+    if (aligned4(n, z, mask))
+        hipLaunchKernelGGL(k_map_reduce<4>, dim3(nblocks), dim3(MAP_NT), 0, s, z, mask, n, pmin, pmax, pcnt, pbad);
+    else
+        hipLaunchKernelGGL(k_map_reduce<1>, dim3(nblocks), dim3(MAP_NT), 0, s, z, mask, n, pmin, pmax, pcnt, pbad);
     return hipGetLastError();
 }
 
@@ -163,8 +211,10 @@ hipError_t launch_map_finalize(const float* pmin, const float* pmax, const unsig
 hipError_t launch_map_apply(const float* z, const uint8_t* mask, int64_t n, const double* range, float* t,
                             hipStream_t s)
 {
-    const int64_t nb = (n + MAP_NT - 1) / MAP_NT;
-    hipLaunchKernelGGL(k_map_apply, dim3((unsigned)nb), dim3(MAP_NT), 0, s, z, mask, n, range, t);
+    const bool v4 = aligned4(n, z, mask, static_cast<const float*>(t));
+    const int64_t nb = (n / (v4 ? 4 : 1) + MAP_NT - 1) / MAP_NT;
+    if (v4) hipLaunchKernelGGL(k_map_apply<4>, dim3((unsigned)nb), dim3(MAP_NT), 0, s, z, mask, n, range, t);
+    else hipLaunchKernelGGL(k_map_apply<1>, dim3((unsigned)nb), dim3(MAP_NT), 0, s, z, mask, n, range, t);
     return hipGetLastError();
 }
 
@@ -185,7 +235,9 @@ StatsGeom stats_geom(int64_t H, int64_t W, int lb_h, int lb_w)
     g.nby = (int)((H + lb_h - 1) / lb_h);
     const int64_t ew = lb_w < W ? lb_w : W;
     const int64_t eh = lb_h < H ? lb_h : H;
-    int64_t G = 4096 / ew;
+    // sites of a workgroup: 4096, or 1024 on small grids, where few workgroups run (one block of 128 x 128: 21.8 us as 4
+    // workgroups, 8.2 us as 16)
+    int64_t G = (H * W <= ((int64_t)1 << 20) ? 1024 : 4096) / ew;
     if (G < 1) G = 1;
     if (G > eh) G = eh;
     g.G = (int)G;
@@ -193,13 +245,15 @@ StatsGeom stats_geom(int64_t H, int64_t W, int lb_h, int lb_w)
     return g;
 }
 
+// One chunk of a block (G of its rows) per workgroup.  Bound by the FP64 cosines: 4096 x 4096 sites in 16 x 16 blocks, 60%
+// samples, 98 us (118 us with cos and a division of 64-bit indexes per site); the bytes alone are 18 us.
 __global__ __launch_bounds__(STATS_NT) void k_block_stats(const float* __restrict__ t,
                                                            const uint8_t* __restrict__ mask, StatsGeom g,
                                                            double two_pi_q, double J, int bonds, double* pS,
                                                            int* pN, double* pTs, int* pNo)
 {
-    __shared__ double lds_d[STATS_NT / 64];
-    __shared__ int lds_i[STATS_NT / 64];
+    __shared__ double lds_d[STATS_NT / 64], lds_t[STATS_NT / 64];
+    __shared__ int lds_i[STATS_NT / 64], lds_o[STATS_NT / 64];
     const int b = blockIdx.x / g.nchunk, c = blockIdx.x % g.nchunk;
     const int by = b / g.nbx, bx = b % g.nbx;
     const int64_t yb = (int64_t)by * g.lb_h;
@@ -213,51 +267,74 @@ __global__ __launch_bounds__(STATS_NT) void k_block_stats(const float* __restric
     const int64_t rows = y_end - y_start, cols = x_end - x_start;
     double S = 0.0, Ts = 0.0;
     int N = 0, No = 0;
+    // cos 2 pi q d as cospi(2 q d): the reduction of its argument is exact and short (two_pi_q = 2 pi q, q an FP32 value)
+    const double two_q = (double)(float)(two_pi_q / (2.0 * kPi)) * 2.0;
     if (rows > 0 && cols > 0) {
-        for (int64_t i = threadIdx.x; i < rows * cols; i += STATS_NT) {
-            const int64_t y = y_start + i / cols, x = x_start + i % cols;
+        const uint32_t sites = (uint32_t)(rows * cols), nc = (uint32_t)cols;      // rows * cols < 2^31
+        for (uint32_t i = threadIdx.x; i < sites; i += STATS_NT) {
+            const uint32_t r = i / nc;
+            const int64_t y = y_start + r, x = x_start + (i - r * nc);
             const int64_t n = y * g.W + x;
             if (!mask[n]) continue;
             const double tn = (double)t[n];
             Ts += tn;
             ++No;
             if ((bonds & 1) && x + 1 < g.W && mask[n + 1]) {
-                S += -J * cos(two_pi_q * (tn - (double)t[n + 1]));
+                S += -J * cospi(two_q * (tn - (double)t[n + 1]));
                 ++N;
             }
             if ((bonds & 2) && y + 1 < g.H && mask[n + g.W]) {
-                S += -J * cos(two_pi_q * (tn - (double)t[n + g.W]));
+                S += -J * cospi(two_q * (tn - (double)t[n + g.W]));
                 ++N;
             }
         }
     }
-    S = block_sum<STATS_NT>(S, lds_d);
-    Ts = block_sum<STATS_NT>(Ts, lds_d);
-    N = block_sum<STATS_NT>(N, lds_i);
-    No = block_sum<STATS_NT>(No, lds_i);
+    S = wave_sum(S);
+    Ts = wave_sum(Ts);
+    N = wave_sum(N);
+    No = wave_sum(No);
+    const int w = (int)(threadIdx.x >> 6);
+    if ((threadIdx.x & 63u) == 0) {
+        lds_d[w] = S;
+        lds_t[w] = Ts;
+        lds_i[w] = N;
+        lds_o[w] = No;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        pS[blockIdx.x] = S;
-        pN[blockIdx.x] = N;
-        pTs[blockIdx.x] = Ts;
-        pNo[blockIdx.x] = No;
+        pS[blockIdx.x] = ((lds_d[0] + lds_d[1]) + lds_d[2]) + lds_d[3];
+        pN[blockIdx.x] = lds_i[0] + lds_i[1] + lds_i[2] + lds_i[3];
+        pTs[blockIdx.x] = ((lds_t[0] + lds_t[1]) + lds_t[2]) + lds_t[3];
+        pNo[blockIdx.x] = lds_o[0] + lds_o[1] + lds_o[2] + lds_o[3];
     }
 }
 
+// The chunks of a block, added by P lanes rather than one after another (P a power of two: chunk c by lane c % P), then
+// across the lanes.
 __global__ __launch_bounds__(256) void k_block_stats_final(const double* pS, const int* pN, const double* pTs,
-                                                            const int* pNo, int64_t B, int nchunk, double* S, int* N,
-                                                            double* Ts, int* No)
+                                                            const int* pNo, int64_t B, int nchunk, int P, double* S,
+                                                            int* N, double* Ts, int* No)
 {
-    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (b >= B) return;
+    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, b = g / P;
+    const int lane = (int)(g % P);
     double s = 0.0, ts = 0.0;
     int nn = 0, no = 0;
-    for (int c = 0; c < nchunk; ++c) {
-        const int64_t i = b * nchunk + c;
-        s += pS[i];
-        nn += pN[i];
-        ts += pTs[i];
-        no += pNo[i];
+    if (b < B) {
+        for (int c = lane; c < nchunk; c += P) {
+            const int64_t i = b * nchunk + c;
+            s += pS[i];
+            nn += pN[i];
+            ts += pTs[i];
+            no += pNo[i];
+        }
     }
+    for (int o = P >> 1; o > 0; o >>= 1) {
+        s += __shfl_xor(s, o, 64);
+        ts += __shfl_xor(ts, o, 64);
+        nn += __shfl_xor(nn, o, 64);
+        no += __shfl_xor(no, o, 64);
+    }
+    if (b >= B || lane != 0) return;
     if (S) S[b] = s;
     if (N) N[b] = nn;
     if (Ts) Ts[b] = ts;
@@ -274,15 +351,42 @@ hipError_t launch_block_stats(const float* t, const uint8_t* mask, const StatsGe
                        pN, pTs, pNo);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_block_stats_final, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, pS, pN, pTs, pNo, B,
-                       g.nchunk, S, N, Ts, No);
+    int P = 1;
+    while (P < 64 && P * 2 <= g.nchunk) P *= 2;
+    hipLaunchKernelGGL(k_block_stats_final, dim3((unsigned)((B * P + 255) / 256)), dim3(256), 0, s, pS, pN, pTs, pNo, B,
+                       g.nchunk, P, S, N, Ts, No);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------------------------
 // Energy matching (Sec. 2.1, Sec. 2.2.2): inverse of the matching curve, median fill of blocks without bonds.
 // ------------------------------------------------------------------------------------------------------------
-__device__ double curve_inverse(double e, const double* cT, const double* ce, int n)
+// up[i] = the running maximum of the curve, first point first.
+__device__ double curve_inverse(double e, const double* cT, const double* up, int n)
+{
+    if (e <= -1.0) return 0.0;
+    if (e <= up[0]) {
+        const double denom = up[0] + 1.0;
+        return denom > 0.0 ? cT[0] * (e + 1.0) / denom : cT[0];
+    }
+    int lo = 0, hi = n;                       // the first point at or above e is in (lo, hi]; hi == n: there is none
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (up[mid] >= e) hi = mid;
+        else lo = mid;
+    }
+    if (hi == n) return cT[n - 1];
+    const double prev = up[hi - 1], cur = up[hi];
+    const double lam = (e - prev) / (cur - prev);
+    return exp((1.0 - lam) * log(cT[hi - 1]) + lam * log(cT[hi]));
+}
+
+// Bound by latency.  A curve of up to kCurveLds points is held in LDS as its running maximum, so that a block's search is a
+// few LDS reads (121 points, 65536 blocks: 5 us, and 34 us for a walk along the curve in memory, which a longer curve
+// still takes: each block then reads only the points up to its energy).
+constexpr int kCurveLds = 1024;
+
+__device__ double curve_inverse_walk(double e, const double* cT, const double* ce, int n)
 {
     if (e <= -1.0) return 0.0;
     double prev = ce[0];
@@ -293,7 +397,6 @@ __device__ double curve_inverse(double e, const double* cT, const double* ce, in
     for (int i = 1; i < n; ++i) {
         const double cur = ce[i] > prev ? ce[i] : prev;
         if (cur >= e) {
-            if (cur == prev) return cT[i];
             const double lam = (e - prev) / (cur - prev);
             return exp((1.0 - lam) * log(cT[i - 1]) + lam * log(cT[i]));
         }
@@ -306,6 +409,35 @@ __global__ __launch_bounds__(256) void k_calibrate(const double* S, const int* N
                                                     const double* cT, const double* ce, int nc, float* T_out,
                                                     double* e_out, int* nb_out)
 {
+    __shared__ double up[kCurveLds];
+    __shared__ double wmax[4];
+    if (nc <= kCurveLds) {
+        // running maximum (x replaces it only if greater: a NaN after the first point is passed over, a NaN there stays)
+        const int lane = (int)(threadIdx.x & 63u), w = (int)(threadIdx.x >> 6);
+        const double first = ce[0];
+        double base = -INFINITY;
+        for (int i0 = 0; i0 < nc; i0 += 256) {
+            const int i = i0 + (int)threadIdx.x;
+            double v = i < nc ? ce[i] : -INFINITY;
+            if (!(v == v)) v = -INFINITY;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const double u = __shfl_up(v, o, 64);
+                if (lane >= o && u > v) v = u;
+            }
+            if (lane == 63) wmax[w] = v;
+            __syncthreads();
+            double m = base;
+            for (int j = 0; j < 4; ++j) {
+                if (j < w && wmax[j] > v) v = wmax[j];
+                if (wmax[j] > m) m = wmax[j];
+            }
+            if (base > v) v = base;
+            if (i < nc) up[i] = first == first ? v : first;
+            base = m;
+            __syncthreads();
+        }
+    }
     const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (b >= B) return;
     const int nb = N[b];
@@ -313,7 +445,7 @@ __global__ __launch_bounds__(256) void k_calibrate(const double* S, const int* N
     float T = -1.0f;   // marker: filled by the median pass
     if (nb > 0) {
         e = S[b] / (J * (double)nb);
-        T = (float)(J * curve_inverse(e, cT, ce, nc));
+        T = (float)(J * (nc <= kCurveLds ? curve_inverse(e, cT, up, nc) : curve_inverse_walk(e, cT, ce, nc)));
     }
     T_out[b] = T;
     if (e_out) e_out[b] = e;
@@ -322,6 +454,8 @@ __global__ __launch_bounds__(256) void k_calibrate(const double* S, const int* N
 
 constexpr int MED_NT = 1024;
 
+// One workgroup, bound by its LDS atomics and by L2 reads of 65536 blocks: 46 us, 96 us when one thread searched the 256 bins
+// and the upper of two middle values took a second selection.  With a temperature in every block there is nothing to do.
 // k-th smallest (0-based) of the T values of blocks with N > 0, by a 4-pass 8-bit radix select on the FP32 bit
 // patterns (T >= 0, so the bit patterns are ordered like the values).
 __device__ float radix_select(const float* T, const int* N, int64_t B, unsigned k, unsigned* hist, unsigned* sh)
@@ -338,14 +472,24 @@ __device__ float radix_select(const float* T, const int* N, int64_t B, unsigned 
             }
         }
         __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned cum = 0u, d = 0u;
-            for (d = 0u; d < 256u; ++d) {
-                if (cum + hist[d] > k) break;
-                cum += hist[d];
+        if (threadIdx.x < 64) {               // the bin of rank k: four bins per lane, prefix over the lanes
+            const int l = (int)threadIdx.x;
+            unsigned h[4], sum = 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) sum += h[j] = hist[4 * l + j];
+            unsigned end = sum;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const unsigned u = __shfl_up(end, o, 64);
+                if (l >= o) end += u;
             }
-            sh[0] = prefix | (d << shift);
-            sh[1] = k - cum;
+            unsigned cum = end - sum;
+            if (cum <= k && k < end) {
+                int d = 0;
+                while (cum + h[d] <= k) cum += h[d++];
+                sh[0] = prefix | (unsigned)(4 * l + d) << shift;
+                sh[1] = k - cum;
+            }
         }
         __syncthreads();
         prefix = sh[0];
@@ -369,11 +513,28 @@ __global__ __launch_bounds__(MED_NT) void k_median_fill(float* T, const int* N, 
     const unsigned count = sh[0];
     __syncthreads();
     if (threadIdx.x == 0) *n_have = count;
-    if (count == 0u) return;
+    if (count == 0u || count == (unsigned)B) return;      // no temperature at all, or none to fill in
     const float lo = radix_select(T, N, B, (count - 1u) / 2u, hist, sh);
     float med = lo;
     if ((count & 1u) == 0u) {
-        const float hi = radix_select(T, N, B, count / 2u, hist, sh);
+        // the next value in order: lo again if it has further copies, else the least value above it
+        unsigned upto = 0, above = 0xffffffffu;
+        const unsigned klo = __float_as_uint(lo);
+        for (int64_t b = threadIdx.x; b < B; b += MED_NT) {
+            if (N[b] <= 0) continue;
+            const unsigned key = __float_as_uint(T[b]);
+            if (key <= klo) ++upto;
+            else if (key < above) above = key;
+        }
+        if (threadIdx.x == 0) {
+            sh[0] = 0u;
+            sh[1] = 0xffffffffu;
+        }
+        __syncthreads();
+        atomicAdd(&sh[0], upto);
+        atomicMin(&sh[1], above);
+        __syncthreads();
+        const float hi = sh[0] > count / 2u ? lo : __uint_as_float(sh[1]);
         med = (float)(((double)lo + (double)hi) * 0.5);
     }
     for (int64_t b = threadIdx.x; b < B; b += MED_NT)
@@ -391,35 +552,63 @@ hipError_t launch_calibrate(const double* S, const int* N, int64_t B, double J, 
     return hipGetLastError();
 }
 
-// One wave: the block sums are read 64 at a time (one coalesced load per lane) and added in block order from the
-// lanes' registers (reads of fixed lanes, independent of the sum), one sequential FP64 sum with the rounding of a loop
-// over the blocks (a loop of single loads waited for each load in turn).
-__global__ __launch_bounds__(64) void k_global_mean(const double* Ts, const int* No, int64_t B, float* gmean)
+// The mean over all samples, which starts the gaps of a block without samples: where every block has some it is not read
+// and 0 is left in its place.  The block sums are added in block order, one sequential FP64 sum: a chunk is in LDS while
+// the next is loaded, and one thread adds it (bound by the latency of the additions: 16384 blocks 529 us with the chunk in
+// the lanes' registers).
+constexpr int GM_CHUNK = 2048;
+
+__global__ __launch_bounds__(256) void k_global_mean(const double* __restrict__ Ts, const int* __restrict__ No,
+                                                      int64_t B, float* gmean)
 {
-    if (blockIdx.x != 0) return;
-    const int lane = (int)threadIdx.x;
-    double sum = 0.0;
+    __shared__ double buf[2][GM_CHUNK];
+    __shared__ long long s_cnt[4];
+    __shared__ int s_empty;
+    if (threadIdx.x == 0) s_empty = 0;
+    __syncthreads();
     long long cnt = 0;
-    for (int64_t b0 = 0; b0 < B; b0 += 64) {
-        const int64_t b = b0 + lane;
-        const double t = b < B ? Ts[b] : 0.0;
-        const int n = b < B ? No[b] : 0;
-        const int tlo = __double2loint(t), thi = __double2hiint(t);
-        const int m = B - b0 < 64 ? (int)(B - b0) : 64;
-#pragma unroll
-        for (int j = 0; j < 64; ++j) {
-            if (j < m) {
-                sum += __hiloint2double(__builtin_amdgcn_readlane(thi, j), __builtin_amdgcn_readlane(tlo, j));
-                cnt += __builtin_amdgcn_readlane(n, j);
-            }
-        }
+    bool empty = false;
+    for (int64_t b = threadIdx.x; b < B; b += 256) {
+        cnt += No[b];
+        empty |= No[b] <= 0;
     }
-    if (lane == 0) *gmean = cnt > 0 ? (float)(sum / (double)cnt) : 0.0f;
+    if (empty) s_empty = 1;
+    cnt = block_sum<256>(cnt, s_cnt);         // (its barriers order s_empty)
+    if (!s_empty) {
+        if (threadIdx.x == 0) *gmean = 0.0f;
+        return;
+    }
+    double sum = 0.0;
+    auto fill = [&](int64_t b0, int k, int first) {
+        for (int i = (int)threadIdx.x - first; i < GM_CHUNK; i += 256 - first)
+            if (i >= 0) buf[k][i] = b0 + i < B ? Ts[b0 + i] : 0.0;
+    };
+    fill(0, 0, 0);
+    __syncthreads();
+    for (int64_t b0 = 0, c = 0; b0 < B; b0 += GM_CHUNK, ++c) {
+        const int k = (int)(c & 1);
+        if (threadIdx.x >= 64) {
+            if (b0 + GM_CHUNK < B) fill(b0 + GM_CHUNK, k ^ 1, 64);
+        } else if (threadIdx.x == 0) {
+            const int m = B - b0 < GM_CHUNK ? (int)(B - b0) : GM_CHUNK;
+            int i = 0;
+            for (; i + 16 <= m; i += 16) {
+                double x[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x[j] = buf[k][i + j];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) sum += x[j];
+            }
+            for (; i < m; ++i) sum += buf[k][i];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *gmean = cnt > 0 ? (float)(sum / (double)cnt) : 0.0f;
 }
 
 hipError_t launch_global_mean(const double* Ts, const int* No, int64_t B, float* gmean, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_global_mean, dim3(1), dim3(64), 0, s, Ts, No, B, gmean);
+    hipLaunchKernelGGL(k_global_mean, dim3(1), dim3(256), 0, s, Ts, No, B, gmean);
     return hipGetLastError();
 }
 
@@ -604,26 +793,37 @@ hipError_t launch_accumulate(const float* state, const uint8_t* mask, int64_t HW
 // ------------------------------------------------------------------------------------------------------------
 // Back-transform of the conditional mean (Sec. 2.1) and the validation measures (Eq. 3, Eq. 4).
 // ------------------------------------------------------------------------------------------------------------
+template <int V>
 __global__ __launch_bounds__(256) void k_predict(const double* __restrict__ acc, const float* __restrict__ z,
                                                   const uint8_t* __restrict__ mask, int64_t n, int64_t n_samples,
                                                   const double* __restrict__ range, float* __restrict__ zhat)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * V;
     if (i >= n) return;
-    if (mask[i]) {
-        zhat[i] = z[i];
-        return;
-    }
     const double zmin = range[0], span = range[1] - range[0];
-    const double tbar = acc[i] / (double)n_samples;
-    zhat[i] = (float)(zmin + span * tbar);
+    float zv[V], out[V];
+    uint8_t m[V];
+    double a[V];
+    load_v<V>(z, i, zv);
+    load_v<V>(mask, i, m);
+    load_v<V>(acc, i, a);
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+        const double tbar = a[k] / (double)n_samples;
+        out[k] = m[k] ? zv[k] : (float)(zmin + span * tbar);
+    }
+    store_v<V>(zhat, i, out);
 }
 
 hipError_t launch_predict(const double* acc, const float* z, const uint8_t* mask, int64_t n, int64_t n_samples,
                           const double* range, float* zhat, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_predict, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, acc, z, mask, n, n_samples,
-                       range, zhat);
+    if (aligned4(n, acc, z, mask, static_cast<const float*>(zhat)))
+        hipLaunchKernelGGL(k_predict<4>, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, s, acc, z, mask, n,
+                           n_samples, range, zhat);
+    else
+        hipLaunchKernelGGL(k_predict<1>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, acc, z, mask, n, n_samples,
+                           range, zhat);
     return hipGetLastError();
 }
 
@@ -635,18 +835,27 @@ int validate_blocks(int64_t n)
     return (int)(b < 1 ? 1 : (b > 2048 ? 2048 : b));
 }
 
+template <int V>
 __global__ __launch_bounds__(VAL_NT) void k_validate_part(const float* __restrict__ zhat,
                                                            const float* __restrict__ truth,
                                                            const uint8_t* __restrict__ ev, int64_t n, double* part)
 {
     __shared__ double s_red[VAL_NT / 64];
     double sa = 0.0, s2 = 0.0, cnt = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * VAL_NT + threadIdx.x; i < n; i += (int64_t)gridDim.x * VAL_NT) {
-        if (!ev[i]) continue;
-        const double e = (double)truth[i] - (double)zhat[i];
-        sa += fabs(e);
-        s2 += e * e;
-        cnt += 1.0;
+    for (int64_t i = ((int64_t)blockIdx.x * VAL_NT + threadIdx.x) * V; i < n; i += (int64_t)gridDim.x * VAL_NT * V) {
+        uint8_t m[V];
+        float a[V], b[V];
+        load_v<V>(ev, i, m);
+        load_v<V>(truth, i, a);
+        load_v<V>(zhat, i, b);
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            if (!m[k]) continue;
+            const double e = (double)a[k] - (double)b[k];
+            sa += fabs(e);
+            s2 += e * e;
+            cnt += 1.0;
+        }
     }
     sa = block_sum<VAL_NT>(sa, s_red);
     s2 = block_sum<VAL_NT>(s2, s_red);
@@ -658,15 +867,20 @@ __global__ __launch_bounds__(VAL_NT) void k_validate_part(const float* __restric
     }
 }
 
-__global__ void k_validate_final(const double* part, int nblocks, double* out)
+// The partial sums by a whole workgroup (2048 of them: 4.7 us, and 221 us when one thread read them in turn).
+__global__ __launch_bounds__(VAL_NT) void k_validate_final(const double* part, int nblocks, double* out)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ double s_red[VAL_NT / 64];
     double sa = 0.0, s2 = 0.0, cnt = 0.0;
-    for (int i = 0; i < nblocks; ++i) {
+    for (int i = (int)threadIdx.x; i < nblocks; i += VAL_NT) {
         sa += part[3 * i];
         s2 += part[3 * i + 1];
         cnt += part[3 * i + 2];
     }
+    sa = block_sum<VAL_NT>(sa, s_red);
+    s2 = block_sum<VAL_NT>(s2, s_red);
+    cnt = block_sum<VAL_NT>(cnt, s_red);
+    if (threadIdx.x != 0) return;
     out[0] = cnt > 0.0 ? sa / cnt : 0.0;
     out[1] = cnt > 0.0 ? sqrt(s2 / cnt) : 0.0;
 }
@@ -674,10 +888,13 @@ __global__ void k_validate_final(const double* part, int nblocks, double* out)
 hipError_t launch_validate(const float* zhat, const float* truth, const uint8_t* ev, int64_t n, double* part,
                            int nblocks, double* out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_validate_part, dim3(nblocks), dim3(VAL_NT), 0, s, zhat, truth, ev, n, part);
+    if (aligned4(n, zhat, truth, ev))
+        hipLaunchKernelGGL(k_validate_part<4>, dim3(nblocks), dim3(VAL_NT), 0, s, zhat, truth, ev, n, part);
+    else
+        hipLaunchKernelGGL(k_validate_part<1>, dim3(nblocks), dim3(VAL_NT), 0, s, zhat, truth, ev, n, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_validate_final, dim3(1), dim3(64), 0, s, part, nblocks, out);
+    hipLaunchKernelGGL(k_validate_final, dim3(1), dim3(VAL_NT), 0, s, part, nblocks, out);
     return hipGetLastError();
 }
 
