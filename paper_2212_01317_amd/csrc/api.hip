@@ -16,6 +16,7 @@
 #include "mpr.h"
 #include "lattice3d.hpp"
 #include "mpr_internal.hpp"
+#include "refcurve.hpp"
 #include "rl_start.hpp"
 #include "tiles.hpp"
 
@@ -231,7 +232,8 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
 }
 
 struct RefWs {
-    float* state;
+    mpr::RefPlan plan;
+    float *state, *state_alt;
     double* part;
     double* esum;
     int nparts;
@@ -239,12 +241,58 @@ struct RefWs {
 size_t ref_ws(Carve& c, int32_t nT, int32_t L, RefWs* w)
 {
     RefWs x;
+    x.plan = mpr::ref_plan(2, L, nT);
     x.state = c.take<float>((int64_t)nT * L * L);
+    x.state_alt = x.plan.strips > 1 ? c.take<float>((int64_t)nT * L * L) : x.state;
     x.nparts = mpr::ref_energy_parts(L);
     x.part = c.take<double>((int64_t)x.nparts * nT);
-    x.esum = c.take<double>(nT);
+    x.esum = c.take<double>((int64_t)nT * std::max(1, x.plan.strips));
     if (w) *w = x;
     return c.used;
+}
+
+size_t ref3_ws(Carve& c, int32_t nT, int32_t L, RefWs* w)
+{
+    RefWs x;
+    const int64_t n = (int64_t)nT * L * L * L;
+    x.plan = mpr::ref_plan(3, L, nT);
+    x.state = c.take<float>(n);
+    x.state_alt = x.plan.strips > 1 ? c.take<float>(n) : x.state;
+    x.nparts = mpr::ref3_energy_parts(L);
+    x.part = c.take<double>((int64_t)x.nparts * nT);
+    x.esum = c.take<double>((int64_t)nT * std::max(1, x.plan.strips));
+    if (w) *w = x;
+    return c.used;
+}
+
+// The chains of a matching curve with several sweeps per launch: a sweep count, two states, one slot per strip.
+hipError_t run_ref_sweeps(int dim, const mpr::RefPlan& plan, const float* T_grid, int nT, int L, int64_t n_therm,
+                          int64_t n_meas, float q, float delta_e, uint64_t seed, float* state, float* state_alt,
+                          double* esum, double inv_norm, double* e_out, hipStream_t s)
+{
+    mpr::RefSweepArgs a;
+    a.Tgrid = T_grid;
+    a.nT = nT;
+    a.L = L;
+    a.n_therm = (uint32_t)n_therm;
+    a.key0 = (uint32_t)(seed & 0xffffffffu);
+    a.key1 = (uint32_t)(seed >> 32);
+    a.q = q;
+    a.delta_e = delta_e;
+    a.two_pi_q = 2.0 * mpr::kPi * (double)q;
+    a.esum = esum;
+    a.src = nullptr;
+    a.dst = state;
+    const int64_t n = n_therm + n_meas;
+    for (int64_t k = 0; k < n; k += a.ns) {
+        a.ns = (int)std::min<int64_t>(plan.depth, n - k);
+        a.sweep = (uint32_t)(k + 1);
+        const hipError_t e = mpr::launch_ref_sweeps(dim, plan, a, s);
+        if (e != hipSuccess) return e;
+        a.src = a.dst;
+        a.dst = a.src == state ? state_alt : state;
+    }
+    return mpr::launch_ref_mean(esum, plan.strips, nT, inv_norm, (double)n_meas, e_out, s);
 }
 
 mpr_status check_ws(void* ws, size_t have, size_t need)
@@ -770,6 +818,12 @@ mpr_status mpr_reference_curve(float q, const float* T_grid, int32_t nT, int32_t
     RefWs w;
     ref_ws(c, nT, L, &w);
     hipStream_t s = S(stream);
+    const double inv_norm = 1.0 / (2.0 * (double)L * (double)L);
+    if (w.plan.strips > 0) {
+        MPR_HIP(run_ref_sweeps(2, w.plan, T_grid, nT, L, n_therm, n_meas, q, mpr::kDeltaE, seed, w.state, w.state_alt,
+                               w.esum, inv_norm, e_out, s));
+        return ok();
+    }
     MPR_HIP(mpr::launch_ref_fill(w.state, (int64_t)nT * L * L, 0.5f, s));
     mpr::RefArgs a;
     a.state = w.state;
@@ -781,7 +835,6 @@ mpr_status mpr_reference_curve(float q, const float* T_grid, int32_t nT, int32_t
     a.q = q;
     a.delta_e = mpr::kDeltaE;
     a.two_pi_q = 2.0 * mpr::kPi * (double)q;
-    const double inv_norm = 1.0 / (2.0 * (double)L * (double)L);
     for (int32_t k = 1; k <= n_therm + n_meas; ++k) {
         a.sweep = (uint32_t)k;
         for (int colour = 0; colour < 2; ++colour) {
@@ -1920,10 +1973,7 @@ size_t mpr_reference_curve3d_workspace_bytes(int32_t nT, int32_t L)
 {
     if (nT < 1 || L < 2) return 0;
     Carve c{nullptr, 0, 0};
-    c.take<float>((int64_t)nT * L * L * L);
-    c.take<double>((int64_t)mpr::ref3_energy_parts(L) * nT);
-    c.take<double>(nT);
-    return c.used;
+    return ref3_ws(c, nT, L, nullptr);
 }
 
 mpr_status mpr_reference_curve3d(float q, const float* T_grid, int32_t nT, int32_t L, int32_t n_therm, int32_t n_meas,
@@ -1937,25 +1987,28 @@ mpr_status mpr_reference_curve3d(float q, const float* T_grid, int32_t nT, int32
     mpr_status st = check_ws(workspace, ws_bytes, mpr_reference_curve3d_workspace_bytes(nT, L));
     if (st != MPR_OK) return st;
     Carve c{static_cast<char*>(workspace), 0, ws_bytes};
-    float* state = c.take<float>((int64_t)nT * L * L * L);
-    const int nparts = mpr::ref3_energy_parts(L);
-    double* part = c.take<double>((int64_t)nparts * nT);
-    double* esum = c.take<double>(nT);
+    RefWs w;
+    ref3_ws(c, nT, L, &w);
     hipStream_t s = S(stream);
-    MPR_HIP(mpr::launch_ref_fill(state, (int64_t)nT * L * L * L, 0.5f, s));
+    const double inv_norm = 1.0 / (3.0 * (double)L * (double)L * (double)L);
+    if (w.plan.strips > 0) {
+        MPR_HIP(run_ref_sweeps(3, w.plan, T_grid, nT, L, n_therm, n_meas, q, mpr::kDeltaE3, seed, w.state, w.state_alt,
+                               w.esum, inv_norm, e_out, s));
+        return ok();
+    }
+    MPR_HIP(mpr::launch_ref_fill(w.state, (int64_t)nT * L * L * L, 0.5f, s));
     const uint32_t key0 = (uint32_t)(seed & 0xffffffffu), key1 = (uint32_t)(seed >> 32);
     const double two_pi_q = 2.0 * mpr::kPi * (double)q;
-    const double inv_norm = 1.0 / (3.0 * (double)L * (double)L * (double)L);
     for (int32_t k = 1; k <= n_therm + n_meas; ++k) {
         for (int colour = 0; colour < 2; ++colour)
-            MPR_HIP(mpr::launch_ref3_half(state, T_grid, nT, L, (uint32_t)k, colour, q, mpr::kDeltaE3, key0, key1,
+            MPR_HIP(mpr::launch_ref3_half(w.state, T_grid, nT, L, (uint32_t)k, colour, q, mpr::kDeltaE3, key0, key1,
                                           two_pi_q, s));
         if (k > n_therm) {
-            MPR_HIP(mpr::launch_ref3_energy(state, L, nT, q, part, nparts, s));
-            MPR_HIP(mpr::launch_ref_accumulate(part, nparts, nT, inv_norm, esum, k == n_therm + 1 ? 1 : 0, s));
+            MPR_HIP(mpr::launch_ref3_energy(w.state, L, nT, q, w.part, w.nparts, s));
+            MPR_HIP(mpr::launch_ref_accumulate(w.part, w.nparts, nT, inv_norm, w.esum, k == n_therm + 1 ? 1 : 0, s));
         }
     }
-    MPR_HIP(mpr::launch_ref_finish(esum, nT, (double)n_meas, e_out, s));
+    MPR_HIP(mpr::launch_ref_finish(w.esum, nT, (double)n_meas, e_out, s));
     return ok();
 }
 
