@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdint>
 
+#include "cos64.hpp"
 #include "metropolis.hpp"
 
 namespace mpr {
@@ -245,11 +246,11 @@ StatsGeom stats_geom(int64_t H, int64_t W, int lb_h, int lb_w)
     return g;
 }
 
-// One chunk of a block (G of its rows) per workgroup.  Bound by the FP64 cosines: 4096 x 4096 sites in 16 x 16 blocks, 60%
-// samples, 98 us (118 us with cos and a division of 64-bit indexes per site); the bytes alone are 18 us.
+// One chunk of a block (G of its rows) per workgroup.  Bound by the FP64 cosines: 4096 x 4096 sites in 32 x 32 blocks, 60%
+// samples, 93 us (119 us with cos and a division of 64-bit indexes per site); the bytes alone are 18 us.
 __global__ __launch_bounds__(STATS_NT) void k_block_stats(const float* __restrict__ t,
                                                            const uint8_t* __restrict__ mask, StatsGeom g,
-                                                           double two_pi_q, double J, int bonds, double* pS,
+                                                           double q, double J, int bonds, double* pS,
                                                            int* pN, double* pTs, int* pNo)
 {
     __shared__ double lds_d[STATS_NT / 64], lds_t[STATS_NT / 64];
@@ -267,8 +268,6 @@ __global__ __launch_bounds__(STATS_NT) void k_block_stats(const float* __restric
     const int64_t rows = y_end - y_start, cols = x_end - x_start;
     double S = 0.0, Ts = 0.0;
     int N = 0, No = 0;
-    // cos 2 pi q d as cospi(2 q d): the reduction of its argument is exact and short (two_pi_q = 2 pi q, q an FP32 value)
-    const double two_q = (double)(float)(two_pi_q / (2.0 * kPi)) * 2.0;
     if (rows > 0 && cols > 0) {
         const uint32_t sites = (uint32_t)(rows * cols), nc = (uint32_t)cols;      // rows * cols < 2^31
         for (uint32_t i = threadIdx.x; i < sites; i += STATS_NT) {
@@ -280,11 +279,11 @@ __global__ __launch_bounds__(STATS_NT) void k_block_stats(const float* __restric
             Ts += tn;
             ++No;
             if ((bonds & 1) && x + 1 < g.W && mask[n + 1]) {
-                S += -J * cospi(two_q * (tn - (double)t[n + 1]));
+                S += -J * cos_turns(q, tn - (double)t[n + 1]);
                 ++N;
             }
             if ((bonds & 2) && y + 1 < g.H && mask[n + g.W]) {
-                S += -J * cospi(two_q * (tn - (double)t[n + g.W]));
+                S += -J * cos_turns(q, tn - (double)t[n + g.W]);
                 ++N;
             }
         }
@@ -347,8 +346,9 @@ hipError_t launch_block_stats(const float* t, const uint8_t* mask, const StatsGe
 {
     const int64_t B = g.B();
     const int64_t nwg = B * g.nchunk;
-    hipLaunchKernelGGL(k_block_stats, dim3((unsigned)nwg), dim3(STATS_NT), 0, s, t, mask, g, two_pi_q, J, bonds, pS,
-                       pN, pTs, pNo);
+    const double q = (double)(float)(two_pi_q / (2.0 * kPi));        // (2 pi q, q an FP32 value)
+    hipLaunchKernelGGL(k_block_stats, dim3((unsigned)nwg), dim3(STATS_NT), 0, s, t, mask, g, q, J, bonds, pS, pN, pTs,
+                       pNo);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int P = 1;
