@@ -180,6 +180,20 @@ int snap_sweeps(int64_t H, int64_t W, int R, int32_t n_samp, int depth)
     return n > 1 && n * R * H * W <= ((int64_t)16 << 20) ? (int)n : 1;
 }
 
+// up to n sweeps from sweep k, but not past the next check of an AUTO stop (the first is at n_fit + n_f)
+int sweeps_to_check(const mpr_sim_config& c, int32_t k, int n)
+{
+    if (!auto_stop(c.stop_mode)) return n;
+    const int64_t first = (int64_t)c.n_fit + c.n_f;
+    return (int)std::min<int64_t>(n, k < first ? first - k : c.n_f - (k - first) % c.n_f);
+}
+
+// Lane sweeps whose energies are reduced together: two small launches (10 to 30 us) then serve several sweeps.
+int energy_sweeps(int64_t nparts, int64_t R)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(8, ((int64_t)4 << 20) / std::max<int64_t>(1, nparts * R)));
+}
+
 struct SimWs {
     StatsWs st;
     double* Ts;
@@ -213,9 +227,10 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     const mpr::RlGeom rg = mpr::rl_geometry(H, W, (int)R);
     int64_t np = nfull;
     if (tiles) np = std::max<int64_t>(np, (int64_t)tg.ntiles * tg.depth);
-    if (rl) np = std::max<int64_t>(np, (int64_t)rg.nbands * rg.nseg);
+    const int es = rl ? energy_sweeps((int64_t)rg.nbands * rg.nseg, R) : 1;
+    if (rl) np = std::max<int64_t>(np, (int64_t)rg.nbands * rg.nseg * es);
     x.epart = c.take<long long>(np * R);
-    x.e_real = c.take<double>(R * (tiles ? tg.depth : 1));
+    x.e_real = c.take<double>(R * (tiles ? tg.depth : es));
     const int64_t cap = auto_stop(cfg->stop_mode) ? cfg->n_max : cfg->n_eq;
     x.series = c.take<double>((cap > 0 ? cap : 0) + 1);
     x.hist = cfg->stop_mode == MPR_STOP_AUTO_CHAIN ? c.take<double>(((cap > 0 ? cap : 0) + 1) * R) : nullptr;
@@ -1016,7 +1031,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     // the realization-lane sweep starts straight in its two lane buffers (both hold the samples); the final state
     // moves back into `state`
     const bool rl = use_rl(H, W, cfg);
-    if (rl) MPR_HIP(mpr::launch_rl_init(ia, mpr::rl_geometry(H, W, R).Rp, w.rl[0], w.rl[1], s));
+    if (rl) MPR_HIP(mpr::launch_lane_start(ia, w.rl[0], w.rl[1], s));
     else MPR_HIP(mpr::launch_init(ia, s));
     const bool directional = c.coupling == MPR_COUPLING_DIRECTIONAL;
     if (directional) {
@@ -1032,9 +1047,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
     if (need_energy) {
-        if (rl)
-            MPR_HIP(mpr::launch_rl_energy_full(w.rl[0], H, W, R, c.q, w.epart, nfull,
-                                               c.init_mode == MPR_INIT_BLOCK_MEAN, s));
+        if (rl) MPR_HIP(mpr::launch_lane_start_energy(ia, w.rl[0], c.q, w.epart, nfull, s));
         else MPR_HIP(start_energy_partials(state, H, W, R, c, w.epart, nfull, s));
         MPR_HIP(mpr::launch_energy_reduce(w.epart, nfull, R, runner.inv_norm, w.e_real, w.series, s));
     }
@@ -1092,16 +1105,19 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(mpr::launch_rl_cells(mask, H, W, w.cells, s));
     }
     const int rl_parts = rl ? ra.nbands * ra.nseg : 0;
-    // sweeps k .. k + n - 1 (n > 1 on the tile sweeps only, at most max_n)
-    const int max_n = rl || dc ? 1 : runner.g.depth;
+    // sweeps k .. k + n - 1, at most max_n (tile sweeps: of one launch; lanes: a launch each, energies reduced together)
+    const int max_n = dc ? 1 : rl ? energy_sweeps(rl_parts, R) : runner.g.depth;
     auto sweep = [&](uint32_t k, int n, bool energy) -> hipError_t {
         if (rl) {
-            ra.sweep = k;
-            hipError_t e = mpr::launch_sweep_rl(ra, w.cells, w.tp, directional ? w.tpd : nullptr, w.rl[rl_cur],
-                                                w.rl[rl_cur ^ 1], energy ? w.epart : nullptr, s);
-            rl_cur ^= 1;
+            hipError_t e = hipSuccess;
+            for (int i = 0; i < n && e == hipSuccess; ++i) {
+                ra.sweep = k + (uint32_t)i;
+                e = mpr::launch_sweep_rl(ra, w.cells, w.tp, directional ? w.tpd : nullptr, w.rl[rl_cur], w.rl[rl_cur ^ 1],
+                                         energy ? w.epart + (int64_t)i * R * rl_parts : nullptr, s);
+                rl_cur ^= 1;
+            }
             if (e == hipSuccess && energy)
-                e = mpr::launch_energy_reduce(w.epart, rl_parts, R, runner.inv_norm, w.e_real, w.series + k, s);
+                e = mpr::launch_energy_reduce_n(w.epart, rl_parts, R, n, runner.inv_norm, w.e_real, w.series + k, s);
             return e;
         }
         if (!dc) return runner.run(k, n, energy ? w.series + k : nullptr);
@@ -1129,12 +1145,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(chains.start(w.hist, R, c.n_fit, s));
     }
     while (k < cap) {
-        // up to the next check (the first is at n_fit + n_f) or the cap
-        int n = std::min<int>(max_n, cap - k);
-        if (auto_stop(c.stop_mode)) {
-            const int64_t first = (int64_t)c.n_fit + c.n_f;
-            n = (int)std::min<int64_t>(n, k < first ? first - k : c.n_f - (k - first) % c.n_f);
-        }
+        const int n = sweeps_to_check(c, k, std::min<int>(max_n, cap - k));
         MPR_HIP(sweep((uint32_t)(k + 1), n, need_energy));
         if (per_chain)
             MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)(k + 1) * R, w.e_real, sizeof(double) * (size_t)R * n,
@@ -1170,11 +1181,13 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     }
     for (int32_t si = 1; si <= (w.snap ? 0 : c.n_samp); ++si) {
         MPR_HIP(sweep((uint32_t)(k_star + si), 1, false));
-        if (rl) MPR_HIP(mpr::launch_rl_accumulate(w.rl[rl_cur], mask, HW, R, si == 1 ? 1 : 0, acc_out, s));
+        if (rl)             // with the last sum the state leaves the lanes too
+            MPR_HIP(mpr::launch_lane_end(w.rl[rl_cur], mask, HW, R, si == 1 ? 1 : 0, si == c.n_samp ? state : nullptr,
+                                         acc_out, s));
         else MPR_HIP(mpr::launch_accumulate(current(), mask, HW, R, si == 1 ? 1 : 0, acc_out, s));
     }
     if (rl) {
-        MPR_HIP(mpr::launch_rl_from_lanes(w.rl[rl_cur], HW, R, state, s));
+        if (c.n_samp == 0) MPR_HIP(mpr::launch_lane_end(w.rl[rl_cur], mask, HW, R, 0, state, nullptr, s));
     } else if (current() != state) {
         MPR_HIP(hipMemcpyAsync(state, current(), sizeof(float) * (size_t)(R * HW), hipMemcpyDeviceToDevice, s));
     }
@@ -1611,22 +1624,19 @@ static mpr_status batched_lanes(const mpr_scene* scenes, int32_t n_scenes, const
         ia.key0 = key0;
         ia.key1 = key1;
         ia.mode = c.init_mode;
-        // (the start goes through the [R][H][W] state here: with many small scenes the per-site kernels of the
-        // plane layout keep more of the device busy than the lane-layout start, which is written for large grids)
-        MPR_HIP(mpr::launch_init(ia, ss));
+        MPR_HIP(mpr::launch_lane_start(ia, w.buf0[i], w.buf1[i], ss));
         MPR_HIP(mpr::launch_tpairs(sc.T_blocks, g.B(), c.J, mpr::kDeltaE * c.J, w.tp[i], ss));
         const int64_t HW = sc.H * sc.W;
         const int64_t nbonds = sc.H * (sc.W - 1) + sc.W * (sc.H - 1);
         const double inv_norm = nbonds > 0 ? 1.0 / (double)nbonds : 0.0;
         if (energy) {
             const int nfull = mpr::energy_full_parts(sc.H, sc.W);
-            MPR_HIP(start_energy_partials(sc.state, sc.H, sc.W, R, c, w.epart[i], nfull, ss));
+            MPR_HIP(mpr::launch_lane_start_energy(ia, w.buf0[i], c.q, w.epart[i], nfull, ss));
             MPR_HIP(mpr::launch_energy_reduce(w.epart[i], nfull, R, inv_norm, w.e_real[i], w.series[i], ss));
         }
         if (c.n_samp == 0) MPR_HIP(hipMemsetAsync(sc.acc, 0, sizeof(double) * (size_t)HW, ss));
         MPR_HIP(mpr::launch_rl_cells(sc.mask, sc.H, sc.W, w.cells[i], ss));
         MPR_HIP(mpr::launch_count_gaps(sc.mask, HW, w.gaps + i, ss));
-        MPR_HIP(mpr::launch_rl_to_lanes(sc.state, HW, R, w.buf0[i], w.buf1[i], ss));
         const mpr::RlGeom rg = mpr::rl_geometry_full(sc.H, sc.W, R);
         mpr::BatchLaneScene& d = hs[i];
         mpr::RlArgs& ra = d.a;
@@ -1761,7 +1771,7 @@ static mpr_status batched_lanes(const mpr_scene* scenes, int32_t n_scenes, const
     bool all_converged = true;
     for (int i = 0; i < n_scenes; ++i) {
         const int total = runs[i].k_star + c.n_samp;
-        MPR_HIP(mpr::launch_rl_from_lanes(hs[i].buf[total & 1], hs[i].HW, R, scenes[i].state, s));
+        MPR_HIP(mpr::launch_lane_end(hs[i].buf[total & 1], scenes[i].mask, hs[i].HW, R, 0, scenes[i].state, nullptr, s));
         if (sweeps_done_out) sweeps_done_out[i] = runs[i].k_star;
         if (converged_out) converged_out[i] = runs[i].converged != 0 ? 1 : 0;
         all_converged &= runs[i].converged != 0;
@@ -1916,9 +1926,10 @@ size_t sim3_ws(Carve& c, int64_t D, int64_t H, int64_t W, int32_t lb_d, int32_t 
     x.cells = c.take<uint32_t>(D * H * g.nbands);
     x.lanes = c.take<float>((int64_t)g.Rp * g.n_all + 2 * mpr::kMargin3);
     if (x.lanes) x.lanes += mpr::kMargin3;
-    const int64_t np = std::max<int64_t>(g.nparts, mpr::energy3_parts(D, H, W));
+    const int es = energy_sweeps(g.nparts, R);
+    const int64_t np = std::max<int64_t>((int64_t)g.nparts * es, mpr::energy3_parts(D, H, W));
     x.epart = c.take<long long>(np * R);
-    x.e_real = c.take<double>(R);
+    x.e_real = c.take<double>((int64_t)R * es);
     const int64_t cap = auto_stop(cfg->stop_mode) ? cfg->n_max : cfg->n_eq;
     x.series = c.take<double>((cap > 0 ? cap : 0) + 1);
     x.hist = cfg->stop_mode == MPR_STOP_AUTO_CHAIN ? c.take<double>(((cap > 0 ? cap : 0) + 1) * R) : nullptr;
@@ -2060,7 +2071,6 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
         MPR_HIP(mpr::launch_global_mean(w.st.Ts, w.st.No, g.B, w.gmean, s));
     }
     mpr::Init3Args ia;
-    ia.state = state;
     ia.t = t;
     ia.mask = mask;
     ia.Ts = w.st.Ts;
@@ -2080,18 +2090,17 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
     ia.key0 = key0;
     ia.key1 = key1;
     ia.mode = c.init_mode;
-    MPR_HIP(mpr::launch_init3(ia, s));
+    MPR_HIP(mpr::launch_lane_start3(ia, w.lanes, s));
     MPR_HIP(mpr::launch_tpairs(T_blocks, g.B, c.J, mpr::kDeltaE3 * c.J, w.tp, s));
     const int64_t nbonds = (W - 1) * H * D + W * (H - 1) * D + W * H * (D - 1);
     const double inv_norm = nbonds > 0 ? 1.0 / (double)nbonds : 0.0;
     const bool need_energy = auto_stop(c.stop_mode) || energy_out != nullptr;
     if (need_energy) {
         const int nfull = mpr::energy3_parts(D, H, W);
-        MPR_HIP(mpr::launch_energy3_full(state, D, H, W, R, c.q, w.epart, nfull, s));
+        MPR_HIP(mpr::launch_lane_start_energy3(ia, w.lanes, c.q, w.epart, nfull, s));
         MPR_HIP(mpr::launch_energy_reduce(w.epart, nfull, R, inv_norm, w.e_real, w.series, s));
     }
     MPR_HIP(mpr::launch_cells3(mask, D, H, W, g.nbands, w.cells, s));
-    MPR_HIP(mpr::launch_rl_to_lanes(state, g.n_all, R, w.lanes, nullptr, s));
 
     mpr::Lat3Args a{};
     a.D = (int)D;
@@ -2120,15 +2129,18 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
     a.Jd = (double)c.J;
     // one sweep: colour 0, then colour 1, each one launch over all row pairs
     a.nrows = (int)((H + 1) / 2);
-    auto sweep = [&](uint32_t k, bool energy) -> hipError_t {
-        a.sweep = k;
-        for (int colour = 0; colour < 2; ++colour) {
-            a.colour = colour;
+    // (sweeps k .. k + n - 1, energies reduced together)
+    const int max_n = energy_sweeps(g.nparts, R);
+    auto sweep = [&](uint32_t k, int n, bool energy) -> hipError_t {
+        for (int i = 0; i < 2 * n; ++i) {
+            a.sweep = k + (uint32_t)(i >> 1);
+            a.colour = i & 1;
             const hipError_t e = mpr::launch_sweep3(a, w.cells, w.tp, w.lanes,
-                                                    energy && colour == 1 ? w.epart : nullptr, s);
+                                                    energy && a.colour == 1 ? w.epart + (int64_t)(i >> 1) * R * g.nparts
+                                                                            : nullptr, s);
             if (e != hipSuccess) return e;
         }
-        if (energy) return mpr::launch_energy_reduce(w.epart, g.nparts, R, inv_norm, w.e_real, w.series + k, s);
+        if (energy) return mpr::launch_energy_reduce_n(w.epart, g.nparts, R, n, inv_norm, w.e_real, w.series + k, s);
         return hipSuccess;
     };
 
@@ -2148,11 +2160,12 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
         MPR_HIP(chains.start(w.hist, R, c.n_fit, s));
     }
     while (k < cap) {
-        ++k;
-        MPR_HIP(sweep((uint32_t)k, need_energy));
+        const int n = sweeps_to_check(c, k, std::min<int>(max_n, cap - k));
+        MPR_HIP(sweep((uint32_t)(k + 1), n, need_energy));
         if (per_chain)
-            MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)k * R, w.e_real, sizeof(double) * (size_t)R,
+            MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)(k + 1) * R, w.e_real, sizeof(double) * (size_t)R * n,
                                    hipMemcpyDeviceToDevice, s));
+        k += n;
         if (auto_stop(c.stop_mode)) {
             if (k >= c.n_fit + c.n_f && (k - c.n_fit) % c.n_f == 0) {
                 bool done = false;
@@ -2172,10 +2185,12 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
     const int32_t k_star = k;
     if (c.n_samp == 0) MPR_HIP(hipMemsetAsync(acc_out, 0, sizeof(double) * (size_t)g.n_all, s));
     for (int32_t si = 1; si <= c.n_samp; ++si) {
-        MPR_HIP(sweep((uint32_t)(k_star + si), false));
-        MPR_HIP(mpr::launch_rl_accumulate(w.lanes, mask, g.n_all, R, si == 1 ? 1 : 0, acc_out, s));
+        MPR_HIP(sweep((uint32_t)(k_star + si), 1, false));
+        // (with the last sum the state leaves the lanes too)
+        MPR_HIP(mpr::launch_lane_end(w.lanes, mask, g.n_all, R, si == 1 ? 1 : 0, si == c.n_samp ? state : nullptr, acc_out,
+                                     s));
     }
-    MPR_HIP(mpr::launch_rl_from_lanes(w.lanes, g.n_all, R, state, s));
+    if (c.n_samp == 0) MPR_HIP(mpr::launch_lane_end(w.lanes, mask, g.n_all, R, 0, state, nullptr, s));
     if (energy_out && need_energy)
         MPR_HIP(hipMemcpyAsync(energy_out, w.series, sizeof(double) * (size_t)(k_star + 1), hipMemcpyDeviceToDevice, s));
     if (sweeps_done_out) *sweeps_done_out = k_star;

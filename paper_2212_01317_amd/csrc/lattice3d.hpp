@@ -36,7 +36,6 @@ hipError_t launch_block_stats3(const float* t, const uint8_t* mask, int64_t D, i
                                int lb_h, int lb_w, double two_pi_q, double J, double* S, int* N, double* Ts, int* No,
                                hipStream_t s);
 struct Init3Args {
-    float* state;                // [R][n]
     const float* t;
     const uint8_t* mask;
     const double* Ts;
@@ -48,11 +47,8 @@ struct Init3Args {
     uint32_t real_offset, scene, key0, key1;
     int mode;
 };
-hipError_t launch_init3(const Init3Args& a, hipStream_t s);
-// fixed-point energy partials of every realization of a [R][n] state (bonds to +x, +y, +z), layout [R][nparts]
+// parts of the energy of a start
 int energy3_parts(int64_t D, int64_t H, int64_t W);
-hipError_t launch_energy3_full(const float* state, int64_t D, int64_t H, int64_t W, int R, float q, long long* partial,
-                               int nparts, hipStream_t s);
 // gap bits of each row's window columns: [(D H) nbands]
 hipError_t launch_cells3(const uint8_t* mask, int64_t D, int64_t H, int64_t W, int nbands, uint32_t* cells,
                          hipStream_t s);

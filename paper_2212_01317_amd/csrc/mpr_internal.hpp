@@ -100,7 +100,6 @@ struct SweepFusedArgs {
     long long* e_partial;  // [R][ntiles] energy of each tile's colour-1 bonds (fixed point, 2^-32), or null
 };
 void fused_geometry(int64_t H, int64_t W, int R, int tile_h, int* ntx, int* nty, int* rchunk, int* nchunks);
-hipError_t launch_sweep_fused(const SweepFusedArgs& a, hipStream_t s);
 // Energies are accumulated in fixed point: each site's bond energy divided by J (at most 4 in magnitude) is
 // rounded to a multiple of 2^-24 (an int32), and the integers are summed exactly (int64 beyond a thread), so the
 // sums do not depend on their order.  kFixUnit converts back.
@@ -150,12 +149,6 @@ struct RlArgs {
 };
 // cells: [(H + 4) * nbands] uint2 (gap bits, sample bits of each wave's window columns, rows -2 .. H + 1)
 hipError_t launch_rl_cells(const uint8_t* mask, int64_t H, int64_t W, uint2* cells, hipStream_t s);
-// [R][HW] -> [HW][Rp] into out (and out2 if not null); pad realizations get 0
-hipError_t launch_rl_to_lanes(const float* in, int64_t HW, int R, float* out, float* out2, hipStream_t s);
-// [HW][Rp] -> [R][HW]
-hipError_t launch_rl_from_lanes(const float* in, int64_t HW, int R, float* out, hipStream_t s);
-hipError_t launch_rl_accumulate(const float* S, const uint8_t* mask, int64_t HW, int R, int first, double* acc,
-                                hipStream_t s);
 // one sweep src -> dst; with epart set, the fixed-point energy of each wave's colour-1 sites goes to
 // epart[r][seg * nbands + band] (layout [R][nbands * nseg])
 // tbd != nullptr: directional coupling with the per-block table tbd (tb is then unused)

@@ -659,81 +659,6 @@ __global__ __launch_bounds__(256) void k_rl_cells(const uint8_t* __restrict__ ma
     cells[i] = make_uint2(gb, sb);
 }
 
-// [R][HW] -> [G][HW][64] (pad realizations get 0) into one or two buffers, 64 sites x 64 realizations per
-// workgroup through LDS.
-__global__ __launch_bounds__(256) void k_rl_to_lanes(const float* __restrict__ in, int64_t HW, int R,
-                                                      float* __restrict__ out, float* __restrict__ out2)
-{
-    __shared__ float tile[64][65];
-    const int64_t n0 = (int64_t)blockIdx.x * 64;
-    const int g = blockIdx.y;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int r = g * 64 + i;
-        const int64_t n = n0 + tx;
-        tile[i][tx] = (r < R && n < HW) ? in[(int64_t)r * HW + n] : 0.0f;
-    }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t n = n0 + i;
-        if (n < HW) {
-            const int64_t o = ((int64_t)g * HW + n) * 64 + tx;
-            out[o] = tile[tx][i];
-            if (out2) out2[o] = tile[tx][i];
-        }
-    }
-}
-
-// [G][HW][64] -> [R][HW]
-__global__ __launch_bounds__(256) void k_rl_from_lanes(const float* __restrict__ in, int64_t HW, int R,
-                                                        float* __restrict__ out)
-{
-    __shared__ float tile[64][65];
-    const int64_t n0 = (int64_t)blockIdx.x * 64;
-    const int g = blockIdx.y;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const int64_t n = n0 + i;
-        tile[i][tx] = n < HW ? in[((int64_t)g * HW + n) * 64 + tx] : 0.0f;
-    }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int r = g * 64 + i;
-        const int64_t n = n0 + tx;
-        if (r < R && n < HW) out[(int64_t)r * HW + n] = tile[tx][i];
-    }
-}
-
-// acc[n] += sum over realizations (in order) of the gap angle; the first pass starts from 0.
-// A workgroup sums 64 consecutive sites: per group of 64 realizations its waves read the gap sites' 256-byte
-// realization rows (one coalesced load per site) into an LDS tile, and lane l of the first wave adds site n0 + l's
-// realizations in order r = 0 .. R - 1 (the order of a loop over the realizations).  Sample sites are not read.
-__global__ __launch_bounds__(256) void k_rl_accumulate(const float* __restrict__ S, const uint8_t* __restrict__ mask,
-                                                        int64_t HW, int R, int first, double* __restrict__ acc)
-{
-    __shared__ float tile[64 * 65];                 // [site][realization], rows padded against bank conflicts
-    const int64_t n0 = (int64_t)blockIdx.x * 64;
-    const int wv = (int)(threadIdx.x >> 6), l = (int)(threadIdx.x & 63u);
-    const int64_t ns = n0 + l;
-    const bool mine = wv == 0 && ns < HW;
-    const bool gap = mine && !mask[ns];
-    double v = gap && !first ? acc[ns] : 0.0;
-    for (int g = 0; g * 64 < R; ++g) {
-        for (int j = wv; j < 64; j += 4) {
-            const int64_t n = n0 + j;
-            if (n < HW && !mask[n]) tile[j * 65 + l] = S[((int64_t)g * HW + n) * 64 + l];
-        }
-        __syncthreads();
-        if (gap) {
-            const int m = R - g * 64 < 64 ? R - g * 64 : 64;
-            for (int k = 0; k < m; ++k) v += (double)tile[l * 65 + k];
-        }
-        __syncthreads();
-    }
-    if (gap) acc[ns] = v;
-    else if (mine && first) acc[ns] = 0.0;
-}
-
 }  // namespace
 
 RlGeom rl_geometry(int64_t H, int64_t W, int R)
@@ -775,30 +700,6 @@ hipError_t launch_rl_cells(const uint8_t* mask, int64_t H, int64_t W, uint2* cel
     const int64_t total = (H + 4) * (int64_t)g.nbands;
     hipLaunchKernelGGL(k_rl_cells, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, mask, (int)H, (int)W,
                        g.nbands, cells);
-    return hipGetLastError();
-}
-
-hipError_t launch_rl_to_lanes(const float* in, int64_t HW, int R, float* out, float* out2, hipStream_t s)
-{
-    const int Rp = (R + 63) / 64 * 64;
-    hipLaunchKernelGGL(k_rl_to_lanes, dim3((unsigned)((HW + 63) / 64), (unsigned)(Rp / 64)), dim3(256), 0, s, in,
-                       HW, R, out, out2);
-    return hipGetLastError();
-}
-
-hipError_t launch_rl_from_lanes(const float* in, int64_t HW, int R, float* out, hipStream_t s)
-{
-    const int Rp = (R + 63) / 64 * 64;
-    hipLaunchKernelGGL(k_rl_from_lanes, dim3((unsigned)((HW + 63) / 64), (unsigned)(Rp / 64)), dim3(256), 0, s, in,
-                       HW, R, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_rl_accumulate(const float* S, const uint8_t* mask, int64_t HW, int R, int first, double* acc,
-                                hipStream_t s)
-{
-    hipLaunchKernelGGL(k_rl_accumulate, dim3((unsigned)((HW + 63) / 64)), dim3(256), 0, s, S, mask, HW, R, first,
-                       acc);
     return hipGetLastError();
 }
 
