@@ -344,6 +344,104 @@ bool equilibrium_reached(double e0, const double* window, int n_fit)
     return beta * sigma0 <= 0.0;
 }
 
+// The energy series as the device writes it into pinned host memory: an AUTO stop reads its window as soon as the values are
+// there, without a copy or a synchronisation (a check: 25 us of copy and wait), and lets the next sweeps run meanwhile.
+// The blocks are kept for later calls, at most kKept of them (of any thread or stream), once every value that the device
+// was to write has been seen.
+class HostSeries {
+public:
+    static constexpr int kSize = 4096, kKept = 8;
+    ~HostSeries()
+    {
+        if (!p_) return;
+        // an early return: nothing may write the block any more when it is handed on
+        if (last_ >= 0 && wait(first_, last_) != hipSuccess) return;
+        std::lock_guard<std::mutex> g(lock());
+        if (count() < kKept) kept()[count()++] = p_;
+        else (void)hipHostFree(p_);
+    }
+    // room for n values, or none (the caller then copies): too many, a stream under capture, no pinned memory
+    bool open(int64_t n, hipStream_t s)
+    {
+        if (n > kSize) return false;
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return false;
+        }
+        {
+            std::lock_guard<std::mutex> g(lock());
+            if (count() > 0) p_ = kept()[--count()];
+        }
+        if (!p_) {
+            void* p = nullptr;
+            const unsigned flags = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+            if (hipHostMalloc(&p, kSize * sizeof(double), flags) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+            p_ = static_cast<double*>(p);
+        }
+        s_ = s;
+        for (int64_t i = 0; i < n; ++i) __atomic_store_n(bits(i), kUnset, __ATOMIC_RELAXED);
+        __atomic_thread_fence(__ATOMIC_SEQ_CST);
+        return true;
+    }
+    explicit operator bool() const { return p_ != nullptr; }
+    // where the launch that is queued next writes values i .. i + n - 1
+    double* at(int64_t i, int n)
+    {
+        if (!p_) return nullptr;
+        first_ = i;
+        last_ = i + n - 1;
+        return p_ + i;
+    }
+    double operator[](int64_t i) const { return p_[i]; }
+    // until values a .. b are there (or the stream has run dry or failed)
+    hipError_t wait(int64_t a, int64_t b)
+    {
+        for (int64_t i = a; i <= b; ++i) {
+            for (uint32_t n = 1; __atomic_load_n(bits(i), __ATOMIC_ACQUIRE) == kUnset; ++n) {
+                if (n % 65536u != 0) {
+                    __builtin_ia32_pause();
+                    continue;
+                }
+                const hipError_t e = hipStreamQuery(s_);
+                if (e == hipErrorNotReady) {
+                    (void)hipGetLastError();
+                    continue;
+                }
+                if (e != hipSuccess) return e;
+                if (__atomic_load_n(bits(i), __ATOMIC_ACQUIRE) == kUnset) return hipErrorUnknown;
+                break;
+            }
+        }
+        return hipSuccess;
+    }
+
+private:
+    static constexpr uint64_t kUnset = ~(uint64_t)0;       // (no arithmetic gives this NaN)
+    uint64_t* bits(int64_t i) const { return reinterpret_cast<uint64_t*>(p_) + i; }
+    static std::mutex& lock()
+    {
+        static std::mutex m;
+        return m;
+    }
+    static double** kept()
+    {
+        static double* k[kKept];
+        return k;
+    }
+    static int& count()
+    {
+        static int n = 0;
+        return n;
+    }
+    double* p_ = nullptr;
+    hipStream_t s_ = nullptr;
+    int64_t first_ = 0, last_ = -1;        // values of the last launch queued
+};
+
 // The per-chain form of the test: every realization applies it to its own energy series, a realization that has
 // passed stays passed, and the scene is in equilibrium once all have passed.  The host keeps e_r(0) and the latch;
 // at a check the last n_fit rows of the [k][R] history come over (hist = the device history).
@@ -466,8 +564,8 @@ struct TileRunner {
     hipError_t plan() { return mpr::launch_tile_plan(a, s); }
 
     // sweeps k .. k + n - 1, n <= depth, in one launch; with e_dst set, their energies go to e_dst[0 .. n); with snap set
-    // (and no e_dst), their states to snap[0 .. n)
-    hipError_t run(uint32_t k, int n, double* e_dst, float* snap = nullptr)
+    // (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
+    hipError_t run(uint32_t k, int n, double* e_dst, float* snap = nullptr, double* e_host = nullptr)
     {
         a.snap = snap;
         a.sweep = k;
@@ -478,7 +576,7 @@ struct TileRunner {
         hipError_t e = mpr::launch_tile_sweeps(a, s);
         if (e != hipSuccess) return e;
         cur ^= 1;
-        if (e_dst) e = mpr::launch_energy_reduce_n(epart, a.ntiles, a.R, n, inv_norm, e_real, e_dst, s);
+        if (e_dst) e = mpr::launch_energy_reduce_n(epart, a.ntiles, a.R, n, inv_norm, e_real, e_dst, e_host, s);
         return e;
     }
 };
@@ -1043,13 +1141,15 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
 
     const bool need_energy = auto_stop(c.stop_mode) || energy_out != nullptr;
     const bool dc = c.order == MPR_ORDER_DC;
+    HostSeries host;
+    if (c.stop_mode == MPR_STOP_AUTO && !dc) host.open((int64_t)c.n_max + 1, s);
     TileRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.plan, w.epart, w.e_real, s);
     if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
     if (need_energy) {
         if (rl) MPR_HIP(mpr::launch_lane_start_energy(ia, w.rl[0], c.q, w.epart, nfull, s));
         else MPR_HIP(start_energy_partials(state, H, W, R, c, w.epart, nfull, s));
-        MPR_HIP(mpr::launch_energy_reduce(w.epart, nfull, R, runner.inv_norm, w.e_real, w.series, s));
+        MPR_HIP(mpr::launch_energy_reduce_n(w.epart, nfull, R, 1, runner.inv_norm, w.e_real, w.series, host.at(0, 1), s));
     }
     // double checkerboard: in place in `state`, energy of the whole grid after the sweep
     mpr::DcArgs da;
@@ -1117,10 +1217,11 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
                 rl_cur ^= 1;
             }
             if (e == hipSuccess && energy)
-                e = mpr::launch_energy_reduce_n(w.epart, rl_parts, R, n, runner.inv_norm, w.e_real, w.series + k, s);
+                e = mpr::launch_energy_reduce_n(w.epart, rl_parts, R, n, runner.inv_norm, w.e_real, w.series + k,
+                                                host.at(k, n), s);
             return e;
         }
-        if (!dc) return runner.run(k, n, energy ? w.series + k : nullptr);
+        if (!dc) return runner.run(k, n, energy ? w.series + k : nullptr, nullptr, energy ? host.at(k, n) : nullptr);
         hipError_t e = mpr::launch_dc_sweep(da, k, s);
         if (e == hipSuccess && energy) e = mpr::launch_energy_full(state, H, W, R, c.q, c.J, w.epart, nfull, s);
         if (e == hipSuccess && energy)
@@ -1137,32 +1238,59 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     const bool per_chain = c.stop_mode == MPR_STOP_AUTO_CHAIN;
     ChainStop chains;
     if (c.stop_mode == MPR_STOP_AUTO) {
-        MPR_HIP(hipMemcpyAsync(&e0, w.series, sizeof(double), hipMemcpyDeviceToHost, s));
         window.resize((size_t)c.n_fit);
+        if (!host) MPR_HIP(hipMemcpyAsync(&e0, w.series, sizeof(double), hipMemcpyDeviceToHost, s));
     }
     if (per_chain) {
         MPR_HIP(hipMemcpyAsync(w.hist, w.e_real, sizeof(double) * (size_t)R, hipMemcpyDeviceToDevice, s));
         MPR_HIP(chains.start(w.hist, R, c.n_fit, s));
     }
+    // While the host looks at a window, the next sweeps run already, into the other state buffer, and are dropped if the
+    // chains have reached equilibrium: one launch, where the sweeps dropped at the end (below 0.1 ms at 2.4e7 sites) are
+    // less than the checks cost (25 us each).  A whole 256 x 256 prediction that
+    // stops by itself: 0.82 ms, 1.20 ms with a copy and a synchronisation at each check.
+    const int ahead_n = !host ? 0 : std::min<int64_t>(rl ? 1 : max_n, 24000000 / std::max<int64_t>(1, HW * R));
+    int32_t queued = 0;
     while (k < cap) {
-        const int n = sweeps_to_check(c, k, std::min<int>(max_n, cap - k));
-        MPR_HIP(sweep((uint32_t)(k + 1), n, need_energy));
-        if (per_chain)
-            MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)(k + 1) * R, w.e_real, sizeof(double) * (size_t)R * n,
-                                   hipMemcpyDeviceToDevice, s));
-        k += n;
+        const int32_t to = k + sweeps_to_check(c, k, cap - k);
+        while (queued < to) {
+            const int n = std::min<int32_t>(max_n, to - queued);
+            MPR_HIP(sweep((uint32_t)(queued + 1), n, need_energy));
+            if (per_chain)
+                MPR_HIP(hipMemcpyAsync(w.hist + (int64_t)(queued + 1) * R, w.e_real, sizeof(double) * (size_t)R * n,
+                                       hipMemcpyDeviceToDevice, s));
+            queued += n;
+        }
+        k = to;
         if (auto_stop(c.stop_mode)) {
             if (k >= c.n_fit + c.n_f && (k - c.n_fit) % c.n_f == 0) {
                 bool done = false;
+                const int32_t first = k - c.n_fit + 1;
+                const int ahead = k < cap ? std::min<int>(ahead_n, sweeps_to_check(c, k, cap - k)) : 0;
                 if (per_chain) {
                     MPR_HIP(chains.check(w.hist, k, s, &done));
+                } else if (host) {
+                    if (ahead > 0) {
+                        MPR_HIP(sweep((uint32_t)(k + 1), ahead, true));
+                        queued = k + ahead;
+                    }
+                    MPR_HIP(host.wait(0, 0));
+                    MPR_HIP(host.wait(first, k));
+                    for (int i = 0; i < c.n_fit; ++i) window[(size_t)i] = host[first + i];
+                    done = equilibrium_reached(host[0], window.data(), c.n_fit);
                 } else {
-                    MPR_HIP(hipMemcpyAsync(window.data(), w.series + (k - c.n_fit + 1), sizeof(double) * c.n_fit,
+                    MPR_HIP(hipMemcpyAsync(window.data(), w.series + first, sizeof(double) * c.n_fit,
                                            hipMemcpyDeviceToHost, s));
                     MPR_HIP(hipStreamSynchronize(s));
                     done = equilibrium_reached(e0, window.data(), c.n_fit);
                 }
-                if (done) break;
+                if (done) {
+                    if (queued > k) {          // back to the state after sweep k
+                        rl_cur ^= 1;
+                        runner.cur ^= 1;
+                    }
+                    break;
+                }
             }
             if (k == c.n_max) converged = false;
         }
@@ -2140,7 +2268,7 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
                                                                             : nullptr, s);
             if (e != hipSuccess) return e;
         }
-        if (energy) return mpr::launch_energy_reduce_n(w.epart, g.nparts, R, n, inv_norm, w.e_real, w.series + k, s);
+        if (energy) return mpr::launch_energy_reduce_n(w.epart, g.nparts, R, n, inv_norm, w.e_real, w.series + k, nullptr, s);
         return hipSuccess;
     };
 

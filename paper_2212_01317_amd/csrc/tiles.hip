@@ -533,7 +533,8 @@ __global__ __launch_bounds__(256) void k_energy_real_n(const long long* __restri
 }
 
 // mean over the realizations, added in order: 64 at a time from the lanes' registers (see k_global_mean)
-__device__ __forceinline__ void ordered_mean(const double* e_real, int R, double* out)
+// (and to host memory, for a host that waits for the value)
+__device__ __forceinline__ void ordered_mean(const double* e_real, int R, double* out, double* host)
 {
     const int lane = (int)(threadIdx.x & 63u);
     double sum = 0.0;
@@ -545,17 +546,20 @@ __device__ __forceinline__ void ordered_mean(const double* e_real, int R, double
         for (int j = 0; j < 64; ++j)
             if (j < m) sum += __hiloint2double(__builtin_amdgcn_readlane(hi, j), __builtin_amdgcn_readlane(lo, j));
     }
-    if (lane == 0) *out = sum / (double)R;
+    if (lane != 0) return;
+    const double mean = sum / (double)R;
+    *out = mean;
+    if (host) __hip_atomic_store(host, mean, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__global__ __launch_bounds__(64) void k_energy_mean_n(const double* e_real, int R, double* e_out)
+__global__ __launch_bounds__(64) void k_energy_mean_n(const double* e_real, int R, double* e_out, double* host)
 {
-    ordered_mean(e_real + (int64_t)blockIdx.x * R, R, e_out + blockIdx.x);
+    ordered_mean(e_real + (int64_t)blockIdx.x * R, R, e_out + blockIdx.x, host ? host + blockIdx.x : nullptr);
 }
 
 // Both steps in one workgroup per sweep, where the partials are few: one wave per realization at a time.
 __global__ __launch_bounds__(1024) void k_energy_small(const long long* __restrict__ partial, int nparts, int R,
-                                                        double inv_norm, double* e_real, double* e_out)
+                                                        double inv_norm, double* e_real, double* e_out, double* host)
 {
     const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6);
     double* const er = e_real + (int64_t)blockIdx.x * R;
@@ -568,7 +572,7 @@ __global__ __launch_bounds__(1024) void k_energy_small(const long long* __restri
         if (lane == 0) er[r] = ((double)s * kFixUnit) * inv_norm;
     }
     __syncthreads();
-    if (wv == 0) ordered_mean(er, R, e_out + blockIdx.x);
+    if (wv == 0) ordered_mean(er, R, e_out + blockIdx.x, host ? host + blockIdx.x : nullptr);
 }
 
 }  // namespace
@@ -637,18 +641,18 @@ hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t
 }
 
 hipError_t launch_energy_reduce_n(const long long* partial, int nparts, int R, int ns, double inv_norm, double* e_real,
-                                  double* e_out, hipStream_t s)
+                                  double* e_out, double* host, hipStream_t s)
 {
     if ((int64_t)nparts * R <= 32768) {
         hipLaunchKernelGGL(k_energy_small, dim3((unsigned)ns), dim3(1024), 0, s, partial, nparts, R, inv_norm, e_real,
-                           e_out);
+                           e_out, host);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_energy_real_n, dim3((unsigned)R, (unsigned)ns), dim3(256), 0, s, partial, nparts, R, inv_norm,
                        e_real);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_energy_mean_n, dim3((unsigned)ns), dim3(64), 0, s, e_real, R, e_out);
+    hipLaunchKernelGGL(k_energy_mean_n, dim3((unsigned)ns), dim3(64), 0, s, e_real, R, e_out, host);
     return hipGetLastError();
 }
 

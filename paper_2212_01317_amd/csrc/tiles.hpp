@@ -40,8 +40,9 @@ hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s);
 // acc[n] += the gap angles of ns states [ns][R][HW], state by state, over the realizations in order; first: from 0
 hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t HW, int R, int ns, bool first,
                                double* acc, hipStream_t s);
-// e_real[i][r] and e_out[i] (mean over the realizations in order) of ns sweeps, from partial [ns][R][nparts]
+// e_real[i][r] and e_out[i] (mean over the realizations in order) of ns sweeps, from partial [ns][R][nparts]; host: the
+// means also go to host[i], in memory that the host reads while the stream runs, or null
 hipError_t launch_energy_reduce_n(const long long* partial, int nparts, int R, int ns, double inv_norm, double* e_real,
-                                  double* e_out, hipStream_t s);
+                                  double* e_out, double* host, hipStream_t s);
 
 }  // namespace mpr
