@@ -176,8 +176,14 @@ bool auto_stop(int32_t stop_mode) { return stop_mode == MPR_STOP_AUTO || stop_mo
 // states are small (their launches would cost more than the extra copy), else one sweep per launch.
 int snap_sweeps(int64_t H, int64_t W, int R, int32_t n_samp, int depth)
 {
-    const int64_t n = std::min<int64_t>(n_samp, depth);
-    return n > 1 && n * R * H * W <= ((int64_t)16 << 20) ? (int)n : 1;
+    const int64_t n = std::min<int64_t>({n_samp, 4 * depth, ((int64_t)16 << 20) / std::max<int64_t>(1, R * H * W)});
+    return n >= std::min<int64_t>(n_samp, depth) && n > 1 ? (int)n : 1;
+}
+
+// Tile sweeps whose energies are reduced together: of four launches where the partials are few.
+int tile_sweeps_together(const mpr::TileGeom& g, int64_t R)
+{
+    return g.depth * (int)std::max<int64_t>(1, std::min<int64_t>(4, ((int64_t)1 << 20) / ((int64_t)g.ntiles * R * g.depth)));
 }
 
 // up to n sweeps from sweep k, but not past the next check of an AUTO stop (the first is at n_fit + n_f)
@@ -226,11 +232,12 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     const bool rl = use_rl(H, W, cfg), tiles = !rl && cfg->order != MPR_ORDER_DC;
     const mpr::RlGeom rg = mpr::rl_geometry(H, W, (int)R);
     int64_t np = nfull;
-    if (tiles) np = std::max<int64_t>(np, (int64_t)tg.ntiles * tg.depth);
+    const int ts = tile_sweeps_together(tg, R);
+    if (tiles) np = std::max<int64_t>(np, (int64_t)tg.ntiles * ts);
     const int es = rl ? energy_sweeps((int64_t)rg.nbands * rg.nseg, R) : 1;
     if (rl) np = std::max<int64_t>(np, (int64_t)rg.nbands * rg.nseg * es);
     x.epart = c.take<long long>(np * R);
-    x.e_real = c.take<double>(R * (tiles ? tg.depth : es));
+    x.e_real = c.take<double>(R * (tiles ? ts : es));
     const int64_t cap = auto_stop(cfg->stop_mode) ? cfg->n_max : cfg->n_eq;
     x.series = c.take<double>((cap > 0 ? cap : 0) + 1);
     x.hist = cfg->stop_mode == MPR_STOP_AUTO_CHAIN ? c.take<double>(((cap > 0 ? cap : 0) + 1) * R) : nullptr;
@@ -563,20 +570,23 @@ struct TileRunner {
     // the update lists; the start must be in place (the samples' angles are read from it)
     hipError_t plan() { return mpr::launch_tile_plan(a, s); }
 
-    // sweeps k .. k + n - 1, n <= depth, in one launch; with e_dst set, their energies go to e_dst[0 .. n); with snap set
-    // (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
+    // sweeps k .. k + n - 1, up to depth of them a launch; with e_dst set, their energies go to e_dst[0 .. n), n at most
+    // tile_sweeps_together; with snap set (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
     hipError_t run(uint32_t k, int n, double* e_dst, float* snap = nullptr, double* e_host = nullptr)
     {
-        a.snap = snap;
-        a.sweep = k;
-        a.ns = n;
-        a.src = buf[cur];
-        a.dst = buf[cur ^ 1];
-        a.e_partial = e_dst ? epart : nullptr;
-        hipError_t e = mpr::launch_tile_sweeps(a, s);
-        if (e != hipSuccess) return e;
-        cur ^= 1;
-        if (e_dst) e = mpr::launch_energy_reduce_n(epart, a.ntiles, a.R, n, inv_norm, e_real, e_dst, e_host, s);
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < n && e == hipSuccess; i += a.ns) {
+            a.ns = std::min(n - i, g.depth);
+            a.sweep = k + (uint32_t)i;
+            a.snap = snap ? snap + (int64_t)i * a.R * a.HW : nullptr;
+            a.src = buf[cur];
+            a.dst = buf[cur ^ 1];
+            a.e_partial = e_dst ? epart + (int64_t)i * a.R * a.ntiles : nullptr;
+            e = mpr::launch_tile_sweeps(a, s);
+            cur ^= 1;
+        }
+        if (e == hipSuccess && e_dst)
+            e = mpr::launch_energy_reduce_n(epart, a.ntiles, a.R, n, inv_norm, e_real, e_dst, e_host, s);
         return e;
     }
 };
@@ -1205,8 +1215,8 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         MPR_HIP(mpr::launch_rl_cells(mask, H, W, w.cells, s));
     }
     const int rl_parts = rl ? ra.nbands * ra.nseg : 0;
-    // sweeps k .. k + n - 1, at most max_n (tile sweeps: of one launch; lanes: a launch each, energies reduced together)
-    const int max_n = dc ? 1 : rl ? energy_sweeps(rl_parts, R) : runner.g.depth;
+    // sweeps k .. k + n - 1, at most max_n (lanes: a launch each), energies reduced together
+    const int max_n = dc ? 1 : rl ? energy_sweeps(rl_parts, R) : tile_sweeps_together(runner.g, R);
     auto sweep = [&](uint32_t k, int n, bool energy) -> hipError_t {
         if (rl) {
             hipError_t e = hipSuccess;
@@ -1249,7 +1259,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     // chains have reached equilibrium: one launch, where the sweeps dropped at the end (below 0.1 ms at 2.4e7 sites) are
     // less than the checks cost (25 us each).  A whole 256 x 256 prediction that
     // stops by itself: 0.82 ms, 1.20 ms with a copy and a synchronisation at each check.
-    const int ahead_n = !host ? 0 : std::min<int64_t>(rl ? 1 : max_n, 24000000 / std::max<int64_t>(1, HW * R));
+    const int ahead_n = !host ? 0 : std::min<int64_t>(rl ? 1 : runner.g.depth, 24000000 / std::max<int64_t>(1, HW * R));
     int32_t queued = 0;
     while (k < cap) {
         const int32_t to = k + sweeps_to_check(c, k, cap - k);

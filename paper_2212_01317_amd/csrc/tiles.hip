@@ -373,6 +373,32 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     const uint32_t* const plan = a.plan + (size_t)tile * C::WORDS;
 
     // ---- staging: cells outside, lists, temperatures, samples ----
+    // The tile's cells are requested first, their loads run under the rest (256 x 256, R = 10: 26.5 us for five sweeps, 27.2
+    // when the cells were loaded after the lists had arrived; of either, 7 us are launch and staging).
+    // my cells: bits 0-15 LDS cell, 16 gap, 17 of the tile; offset within a realization (H W < 2^31)
+    uint32_t cell[C::CPT];
+    int off[C::CPT];
+    const float* __restrict__ src0 = a.src + (int64_t)r0 * a.HW;
+    float pre[C::CPT];
+    uint8_t sample[C::CPT];
+#pragma unroll
+    for (int k = 0; k < C::CPT; ++k) {
+        const int i = tid + k * kNT;
+        const int yl = i / C::RW, xl = i % C::RW;
+        const int gy = box.ty0 - C::HALO + yl, gx = box.tx0 - C::HALO + xl;
+        const int d = ring(yl - C::HALO, xl - C::HALO);
+        cell[k] = 0u;
+        off[k] = 0;
+        pre[k] = 0.0f;
+        sample[k] = 0;
+        if (yl < C::RH && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W && d <= 2 * a.ns) {
+            cell[k] = (uint32_t)(((yl + xl) & 1) * C::CELLS + yl * C::CW + (xl >> 1) + C::LEAD) | 1u << 16 |
+                      (d == 0 ? 1u << 17 : 0u);
+            off[k] = gy * a.W + gx;
+            pre[k] = src0[off[k]];
+            sample[k] = a.mask[off[k]];
+        }
+    }
     for (int i = tid; i < 2 * C::CELLS; i += kNT) {
         L.cs[i] = make_float2(0.0f, 0.0f);
         L.t[i] = -0.0f;
@@ -403,31 +429,15 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         }
     }
     __syncthreads();
-    // my cells: bits 0-15 LDS cell, 16 gap, 17 of the tile; offset within a realization (H W < 2^31)
-    uint32_t cell[C::CPT];
-    int off[C::CPT];
-    const float* __restrict__ src0 = a.src + (int64_t)r0 * a.HW;
-    float pre[C::CPT];
 #pragma unroll
     for (int k = 0; k < C::CPT; ++k) {
-        const int i = tid + k * kNT;
-        const int yl = i / C::RW, xl = i % C::RW;
-        const int gy = box.ty0 - C::HALO + yl, gx = box.tx0 - C::HALO + xl;
-        const int d = ring(yl - C::HALO, xl - C::HALO);
-        cell[k] = 0u;
-        off[k] = 0;
-        pre[k] = 0.0f;
-        if (yl < C::RH && gy >= 0 && gy < a.H && gx >= 0 && gx < a.W && d <= 2 * a.ns) {
-            const int li = ((yl + xl) & 1) * C::CELLS + yl * C::CW + (xl >> 1) + C::LEAD;
-            off[k] = gy * a.W + gx;
-            pre[k] = src0[off[k]];
-            if (a.mask[off[k]]) {
-                const float ang = a.q * pre[k];
-                L.t[li] = -pre[k];
-                L.cs[li] = make_float2(cos_rev(ang), sin_rev(ang));
-            } else {
-                cell[k] = (uint32_t)li | 1u << 16 | (d == 0 ? 1u << 17 : 0u);
-            }
+        if (sample[k] != 0) {
+            const int li = (int)(cell[k] & 0xffffu);
+            const float ang = a.q * pre[k];
+            L.t[li] = -pre[k];
+            L.cs[li] = make_float2(cos_rev(ang), sin_rev(ang));
+            cell[k] = 0u;
+            off[k] = 0;
         }
     }
     // the random-stream counter of a pair is row Mw + group; with b its lowest cell and q that cell's row, the group is
@@ -493,7 +503,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 
 // Sampling: one launch for the states of several sweeps (acc[n] is the sum over the states and, within a state, over the
 // realizations in order, as with one launch per sweep).  Launches and latency bound the small grids it is for: 128 x 128,
-// R = 10, 100 + 100 sweeps take 2.15 ms with a launch of both kernels per sampling sweep and 1.24 ms with one per five.
+// R = 10, 100 + 100 sweeps take 2.15 ms with a launch of both kernels per sampling sweep, 1.20 ms with one per five and
+// 1.09 ms with a sum (and a reduction of energies) per twenty.
 __global__ __launch_bounds__(256) void k_accumulate_n(const float* __restrict__ states, const uint8_t* __restrict__ mask,
                                                        int64_t HW, int64_t rows, int first, double* __restrict__ acc)
 {
@@ -506,12 +517,12 @@ __global__ __launch_bounds__(256) void k_accumulate_n(const float* __restrict__ 
     double v = first ? 0.0 : acc[n];
     const float* p = states + n;
     int64_t i = 0;
-    for (; i + 8 <= rows; i += 8) {           // eight loads in flight, added in order
-        float x[8];
+    for (; i + 16 <= rows; i += 16) {         // sixteen loads in flight, added in order
+        float x[16];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) x[k] = p[(i + k) * HW];
+        for (int k = 0; k < 16; ++k) x[k] = p[(i + k) * HW];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v += (double)x[k];
+        for (int k = 0; k < 16; ++k) v += (double)x[k];
     }
     for (; i < rows; ++i) v += (double)p[i * HW];
     acc[n] = v;
