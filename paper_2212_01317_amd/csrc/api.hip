@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "batched.hpp"
+#include "dc.hpp"
 #include "mpr.h"
 #include "lattice3d.hpp"
 #include "mpr_internal.hpp"
@@ -216,6 +217,7 @@ struct SimWs {
     mpr::TBandDir* tpd; // directional coupling: per-block table
     float* rl[2];       // [HW][Rp] state buffers of the realization-lane sweep
     uint2* cells;       // its per-row window bits
+    mpr::DcPlan dc;     // update lists of the double checkerboard
 };
 size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const mpr_sim_config* cfg, SimWs* w)
 {
@@ -249,6 +251,12 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     x.rl[0] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
     x.rl[1] = rl ? c.take<float>(H * W * rg.Rp) : nullptr;
     x.cells = rl ? c.take<uint2>((H + 4) * rg.nbands) : nullptr;
+    x.dc = mpr::DcPlan{nullptr, nullptr, 0};
+    if (cfg->order == MPR_ORDER_DC) {
+        x.dc.cap = H * ((W + 3) / 4);
+        x.dc.list = c.take<uint32_t>(4 * x.dc.cap);
+        x.dc.count = c.take<uint32_t>(8);
+    }
     if (w) *w = x;
     return c.used;
 }
@@ -1184,6 +1192,8 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     da.delta_e = mpr::kDeltaE * c.J;
     da.two_pi_q = 2.0 * mpr::kPi * (double)c.q;
     da.Jd = (double)c.J;
+    da.plan = w.dc;
+    if (dc) MPR_HIP(mpr::launch_dc_plan(da, s));
     // realization-lane sweep: sweeps alternate between the two [HW][Rp] buffers
     mpr::RlArgs ra{};
     int rl_cur = 0;
@@ -1235,7 +1245,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
         hipError_t e = mpr::launch_dc_sweep(da, k, s);
         if (e == hipSuccess && energy) e = mpr::launch_energy_full(state, H, W, R, c.q, c.J, w.epart, nfull, s);
         if (e == hipSuccess && energy)
-            e = mpr::launch_energy_reduce(w.epart, nfull, R, runner.inv_norm, w.e_real, w.series + k, s);
+            e = mpr::launch_energy_reduce_n(w.epart, nfull, R, 1, runner.inv_norm, w.e_real, w.series + k, nullptr, s);
         return e;
     };
     auto current = [&]() -> float* { return dc ? state : runner.current(); };

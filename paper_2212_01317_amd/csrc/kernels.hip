@@ -712,13 +712,15 @@ __global__ __launch_bounds__(EN_NT) void k_energy_full(const float* __restrict__
     const int r = blockIdx.y;
     const int64_t HW = H * W;
     const float* st = state + (int64_t)r * HW;
+    // (32-bit indexes: H W < 2^31)
+    const uint32_t Wu = (uint32_t)W, last = (uint32_t)(HW - W);
     long long acc = 0;
-    for (int64_t n = (int64_t)blockIdx.x * EN_NT + threadIdx.x; n < HW; n += (int64_t)gridDim.x * EN_NT) {
-        const int64_t y = n / W, x = n - y * W;
+    for (uint32_t n = blockIdx.x * (uint32_t)EN_NT + threadIdx.x; n < (uint32_t)HW; n += gridDim.x * (uint32_t)EN_NT) {
+        const uint32_t x = n - n / Wu * Wu;
         const float tn = st[n];
         float e = 0.0f;                                   // energy of the site's right and lower bonds / J
-        if (x + 1 < W) e -= cos_rev(q * (tn - st[n + 1]));
-        if (y + 1 < H) e -= cos_rev(q * (tn - st[n + W]));
+        if (x + 1 < Wu) e -= cos_rev(q * (tn - st[n + 1]));
+        if (n < last) e -= cos_rev(q * (tn - st[n + Wu]));
         acc += fix24(e);
     }
     const long long tot = block_sum<EN_NT>(acc, s_red);
