@@ -619,52 +619,32 @@ size_t sweep_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, cons
 }
 
 struct BatchWs {
-    mpr::BatchScene* scenes;
-    mpr::BatchRun* runs;
-    int* order;
-    int64_t* prefix;
-    mpr::BatchCtl* ctl;
+    mpr::TileScene* scenes;
+    int* list;
+    uint32_t* prefix;
+    double* means;        // [1 + ring][n]
+    int ring;             // sweeps whose means are at hand: the window of a check, a launch's at least
     StatsWs st;           // init scratch, sized for the largest scene
     double* Ts;
     int* No;
     float* gmean;
     std::vector<mpr::TBand*> tp;
     std::vector<float*> alt;
+    std::vector<uint32_t*> plan;
     std::vector<long long*> epart;
     std::vector<double*> e_real, series;
 };
-
-void batch_geom(int64_t H, int64_t W, int R, int tile_h, int* ntx, int* nty, int* ntiles, int* rchunk, int* nchunks)
-{
-    mpr::fused_geometry(H, W, R, tile_h, ntx, nty, rchunk, nchunks);
-    *ntiles = (*ntx) * (*nty);
-}
-
-// Realization chunk of every work item in a batch: the scenes supply the parallelism, so an item covers as many
-// realizations as possible (its LDS set-up is then shared by all of them), down to what keeps at least 8 items per
-// workgroup slot of the persistent grid.
-int batch_rchunk(const mpr_scene* sc, int n, int R, int tile_h)
-{
-    int64_t tiles = 0;
-    for (int i = 0; i < n; ++i) {
-        int ntx, nty, nt, rc, nc;
-        batch_geom(sc[i].H, sc[i].W, R, tile_h, &ntx, &nty, &nt, &rc, &nc);
-        tiles += nt;
-    }
-    int rc = std::min(R, 64);
-    while (rc > 1 && tiles * ((R + rc - 1) / rc) < 8 * 1024) rc = (rc + 1) / 2;
-    return rc;
-}
 
 size_t batch_ws(Carve& c, const mpr_scene* sc, int n, const mpr_sim_config* cfg, BatchWs* w)
 {
     BatchWs x;
     const int64_t R = cfg->n_real > 0 ? cfg->n_real : 1;
-    x.scenes = c.take<mpr::BatchScene>(n);
-    x.runs = c.take<mpr::BatchRun>(n);
-    x.order = c.take<int>(n);
-    x.prefix = c.take<int64_t>(n + 1);
-    x.ctl = c.take<mpr::BatchCtl>(1);
+    const int64_t cap = cfg->stop_mode == MPR_STOP_AUTO ? cfg->n_max : cfg->n_eq;
+    x.scenes = c.take<mpr::TileScene>(n);
+    x.list = c.take<int>(n);
+    x.prefix = c.take<uint32_t>(n + 1);
+    x.ring = std::max(cfg->stop_mode == MPR_STOP_AUTO ? cfg->n_fit : 1, mpr::tile_geometry(1, 1, (int)R).depth);
+    x.means = c.take<double>(((int64_t)x.ring + 1) * n);
     int64_t max_np = 1, max_B = 1;
     for (int i = 0; i < n; ++i) {
         mpr::StatsGeom g = mpr::stats_geom(sc[i].H, sc[i].W, sc[i].lb_h, sc[i].lb_w);
@@ -678,17 +658,15 @@ size_t batch_ws(Carve& c, const mpr_scene* sc, int n, const mpr_sim_config* cfg,
     x.Ts = c.take<double>(max_B);
     x.No = c.take<int>(max_B);
     x.gmean = c.take<float>(1);
-    const int64_t cap = cfg->stop_mode == MPR_STOP_AUTO ? cfg->n_max : cfg->n_eq;
     for (int i = 0; i < n; ++i) {
         const int64_t H = sc[i].H, W = sc[i].W;
+        const mpr::TileGeom g = mpr::tile_geometry(H, W, (int)R);
         x.tp.push_back(c.take<mpr::TBand>(nblocks_of(H, W, sc[i].lb_h, sc[i].lb_w)));
         x.alt.push_back(c.take<float>(R * H * W));
-        int ntx, nty, nt16, nt32, rc, nc;
-        batch_geom(H, W, (int)R, 16, &ntx, &nty, &nt16, &rc, &nc);
-        batch_geom(H, W, (int)R, 32, &ntx, &nty, &nt32, &rc, &nc);
-        const int64_t np = std::max<int64_t>(std::max(nt16, nt32), mpr::energy_full_parts(H, W));
+        x.plan.push_back(c.take<uint32_t>(g.plan_words));
+        const int64_t np = std::max<int64_t>((int64_t)g.ntiles * g.depth, mpr::energy_full_parts(H, W));
         x.epart.push_back(c.take<long long>(np * R));
-        x.e_real.push_back(c.take<double>(R));
+        x.e_real.push_back(c.take<double>(R * g.depth));
         x.series.push_back(sc[i].energy ? sc[i].energy : c.take<double>((cap > 0 ? cap : 0) + 1));
     }
     if (w) *w = std::move(x);
@@ -1464,7 +1442,7 @@ static mpr_status check_batched(const mpr_scene* scenes, int32_t n_scenes, const
     return MPR_OK;
 }
 
-// The persistent tile-kernel batch over the scenes given (all of them run on the tile kernel).
+// The batch on the tile sweeps.
 static size_t batched_tiles_ws(const mpr_scene* scenes, int32_t n_scenes, const mpr_sim_config* cfg)
 {
     Carve c{nullptr, 0, 0};
@@ -1489,13 +1467,21 @@ static mpr_status batched_tiles(const mpr_scene* scenes, int32_t n_scenes, const
     const bool energy = c.stop_mode == MPR_STOP_AUTO;
     bool any_energy_out = false;
     for (int i = 0; i < n_scenes; ++i) any_energy_out |= scenes[i].energy != nullptr;
+    const bool need_energy = energy || any_energy_out;
 
-    // ---- per-scene start, temperatures, e(0) ----
-    const int rchunk_v[2] = {batch_rchunk(scenes, n_scenes, R, 16), batch_rchunk(scenes, n_scenes, R, 32)};
-    std::vector<mpr::BatchScene> hs(n_scenes);
-    std::vector<int64_t> work16(n_scenes), work32(n_scenes);
+    // ---- per-scene start, temperatures, e(0), update lists ----
+    // the scenes supply the parallelism: an item covers as many realizations as leave about two rounds of workgroups (their
+    // staging is shared)
+    int64_t all_tiles = 0;
+    for (int i = 0; i < n_scenes; ++i) all_tiles += mpr::tile_geometry(scenes[i].H, scenes[i].W, R).ntiles;
+    const int rchunk = (int)std::max<int64_t>(1, std::min<int64_t>({all_tiles * R / 1024, R, 64}));
+    std::vector<mpr::TileScene> hs(n_scenes);
+    std::vector<uint32_t> work(n_scenes);
+    bool table = true;
+    int max_blocks = 1, depth = 1;
     for (int i = 0; i < n_scenes; ++i) {
         const mpr_scene& sc = scenes[i];
+        const int64_t HW = sc.H * sc.W;
         mpr::StatsGeom g = mpr::stats_geom(sc.H, sc.W, sc.lb_h, sc.lb_w);
         if (c.init_mode == MPR_INIT_BLOCK_MEAN) {
             MPR_HIP(mpr::launch_block_stats(sc.t, sc.mask, g, 2.0 * mpr::kPi * (double)c.q, (double)c.J, w.st.pS,
@@ -1523,171 +1509,117 @@ static mpr_status batched_tiles(const mpr_scene* scenes, int32_t n_scenes, const
         ia.mode = c.init_mode;
         MPR_HIP(mpr::launch_init(ia, s));
         MPR_HIP(mpr::launch_tpairs(sc.T_blocks, g.B(), c.J, mpr::kDeltaE * c.J, w.tp[i], s));
-        const int64_t nbonds = sc.H * (sc.W - 1) + sc.W * (sc.H - 1);
-        const double inv_norm = nbonds > 0 ? 1.0 / (double)nbonds : 0.0;
-        if (energy || sc.energy) {
+        TileRunner run(sc.state, w.alt[i], sc.mask, sc.H, sc.W, w.tp[i], sc.lb_h, sc.lb_w, c, w.plan[i], w.epart[i],
+                       w.e_real[i], s);
+        run.a.scene = sc.scene_id;
+        run.a.src = sc.state;
+        run.a.dst = w.alt[i];
+        run.a.e_partial = w.epart[i];
+        run.a.rchunk = rchunk;
+        run.a.nchunks = (R + rchunk - 1) / rchunk;
+        MPR_HIP(run.plan());
+        if (need_energy) {
             const int nfull = mpr::energy_full_parts(sc.H, sc.W);
             MPR_HIP(start_energy_partials(sc.state, sc.H, sc.W, R, c, w.epart[i], nfull, s));
-            MPR_HIP(mpr::launch_energy_reduce(w.epart[i], nfull, R, inv_norm, w.e_real[i], w.series[i], s));
+            MPR_HIP(mpr::launch_energy_reduce_n(w.epart[i], nfull, R, 1, run.inv_norm, w.e_real[i], w.series[i], w.means + i,
+                                                s));
         }
-        if (c.n_samp == 0) MPR_HIP(hipMemsetAsync(sc.acc, 0, sizeof(double) * (size_t)(sc.H * sc.W), s));
-        mpr::BatchScene& d = hs[i];
-        d.t = sc.t;
-        d.mask = sc.mask;
-        d.tp = w.tp[i];
-        d.buf[0] = sc.state;
-        d.buf[1] = w.alt[i];
-        d.acc = sc.acc;
-        d.epart = w.epart[i];
+        if (c.n_samp == 0) MPR_HIP(hipMemsetAsync(sc.acc, 0, sizeof(double) * (size_t)HW, s));
+        mpr::TileScene& d = hs[i];
+        d.a[0] = run.a;
+        d.a[1] = run.a;
+        d.a[1].src = w.alt[i];
+        d.a[1].dst = sc.state;
         d.e_real = w.e_real[i];
         d.series = w.series[i];
-        d.H = (int)sc.H;
-        d.W = (int)sc.W;
-        d.lb_h = sc.lb_h;
-        d.lb_w = sc.lb_w;
-        d.nbx = g.nbx;
-        d.Mw = (int)((sc.W + 3) / 4);
-        for (int v = 0; v < 2; ++v) {
-            int ntx, nty, nt, rc, nc;
-            batch_geom(sc.H, sc.W, R, v ? 32 : 16, &ntx, &nty, &nt, &rc, &nc);
-            rc = rchunk_v[v];
-            nc = (R + rc - 1) / rc;
-            d.ntx = ntx;
-            d.nty[v] = nty;
-            d.ntiles[v] = nt;
-            d.rchunk[v] = rc;
-            d.nchunks[v] = nc;
-        }
-        work16[i] = (int64_t)d.ntiles[0] * d.nchunks[0];
-        work32[i] = (int64_t)d.ntiles[1] * d.nchunks[1];
-        d.HW = sc.H * sc.W;
-        d.scene = sc.scene_id;
-        d.inv_norm = inv_norm;
+        d.acc = sc.acc;
+        d.inv_norm = run.inv_norm;
+        work[i] = (uint32_t)run.a.ntiles * (uint32_t)run.a.nchunks;
+        table = table && mpr::tile_uses_table(run.a);
+        max_blocks = std::max<int>(max_blocks, (int)std::min<int64_t>((HW + 255) / 256, 1024));
+        depth = run.g.depth;
     }
+    if (tile_h_used_out) *tile_h_used_out = tile_h == 0 ? 32 : tile_h;     // (the tile is 64 x 32; the results depend on neither)
+    MPR_HIP(hipMemcpyAsync(w.scenes, hs.data(), sizeof(mpr::TileScene) * n_scenes, hipMemcpyHostToDevice, s));
+
+    // ---- all running scenes advance together, up to the next check ----
+    mpr::TileBatch b{w.scenes, w.list, w.prefix, 0, 0, 0u, 1, table};
+    uint32_t total = 0;
+    std::vector<uint32_t> prefix;
+    auto upload = [&](const std::vector<int>& list) -> hipError_t {
+        prefix.assign(1, 0u);
+        for (int i : list) prefix.push_back(prefix.back() + work[i]);
+        total = prefix.back();
+        b.n = (int)list.size();
+        if (b.n == 0) return hipSuccess;
+        hipError_t e = hipMemcpyAsync(w.list, list.data(), sizeof(int) * list.size(), hipMemcpyHostToDevice, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(w.prefix, prefix.data(), sizeof(uint32_t) * prefix.size(), hipMemcpyHostToDevice, s);
+        return e == hipSuccess ? hipStreamSynchronize(s) : e;              // the host arrays must outlive the copies
+    };
     // largest scenes first
-    std::vector<int> order(n_scenes);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return work32[a] > work32[b]; });
-    int variant = tile_h == 16 ? 0 : 1;
-    const int first_variant = tile_h == 0 ? 0 : variant;
-    std::vector<int64_t> prefix(n_scenes + 1, 0);
-    for (int i = 0; i < n_scenes; ++i)
-        prefix[i + 1] = prefix[i] + (first_variant ? work32[order[i]] : work16[order[i]]);
-    std::vector<mpr::BatchRun> runs(n_scenes, mpr::BatchRun{0, 0, 0, 1});
-    mpr::BatchCtl ctl{0, n_scenes, 0ull};
-    MPR_HIP(hipMemcpyAsync(w.scenes, hs.data(), sizeof(mpr::BatchScene) * n_scenes, hipMemcpyHostToDevice, s));
-    MPR_HIP(hipMemcpyAsync(w.runs, runs.data(), sizeof(mpr::BatchRun) * n_scenes, hipMemcpyHostToDevice, s));
-    MPR_HIP(hipMemcpyAsync(w.order, order.data(), sizeof(int) * n_scenes, hipMemcpyHostToDevice, s));
-    MPR_HIP(hipMemcpyAsync(w.prefix, prefix.data(), sizeof(int64_t) * (n_scenes + 1), hipMemcpyHostToDevice, s));
-    MPR_HIP(hipMemcpyAsync(w.ctl, &ctl, sizeof ctl, hipMemcpyHostToDevice, s));
-    MPR_HIP(hipStreamSynchronize(s));     // the host arrays above must outlive the copies
-
-    mpr::BatchDev b;
-    b.scenes = w.scenes;
-    b.runs = w.runs;
-    b.order = w.order;
-    b.prefix = w.prefix;
-    b.ctl = w.ctl;
-    b.n = n_scenes;
-    b.cfg.R = R;
-    b.cfg.real_offset = (uint32_t)c.real_offset;
-    b.cfg.key0 = key0;
-    b.cfg.key1 = key1;
-    b.cfg.q = c.q;
-    b.cfg.J = c.J;
-    b.cfg.delta_e = mpr::kDeltaE * c.J;
-    b.cfg.two_pi_q = 2.0 * mpr::kPi * (double)c.q;
-    b.cfg.Jd = (double)c.J;
-    b.cfg.energy = (energy || any_energy_out) ? 1 : 0;
-    b.cfg.stop_mode = c.stop_mode;
-    b.cfg.n_fit = c.n_fit;
-    b.cfg.n_f = c.n_f;
-    b.cfg.n_max = c.n_max;
-    b.cfg.n_eq = c.n_eq;
-    b.cfg.n_samp = c.n_samp;
-    int max_hw_blocks = 1;
-    for (int i = 0; i < n_scenes; ++i)
-        max_hw_blocks = std::max<int>(max_hw_blocks, (int)std::min<int64_t>((hs[i].HW + 255) / 256, 1024));
-    const int grid = 256 * 4;              // four workgroups per CU, persistent
+    std::vector<int> active(n_scenes), finished, rest;
+    std::iota(active.begin(), active.end(), 0);
+    std::stable_sort(active.begin(), active.end(), [&](int x, int y) { return work[x] > work[y]; });
+    MPR_HIP(upload(active));
     const int32_t cap = c.stop_mode == MPR_STOP_AUTO ? c.n_max : c.n_eq;
-    const int32_t total_max = cap + c.n_samp;
-    int32_t done = 0;
-
-    // ---- tile-height autotuning on the first two (real) sweeps ----
-    if (tile_h == 0) {
-        hipEvent_t ev[3];
-        for (auto& e : ev) MPR_HIP(hipEventCreate(&e));
-        MPR_HIP(hipEventRecord(ev[0], s));
-        MPR_HIP(mpr::launch_batch_step(b, 0, 1, grid, max_hw_blocks, s));
-        MPR_HIP(hipEventRecord(ev[1], s));
-        MPR_HIP(mpr::launch_batch_step(b, 1, 1, grid, max_hw_blocks, s));
-        MPR_HIP(hipEventRecord(ev[2], s));
-        MPR_HIP(hipEventSynchronize(ev[2]));
-        float t16 = 0.f, t32 = 0.f;
-        MPR_HIP(hipEventElapsedTime(&t16, ev[0], ev[1]));
-        MPR_HIP(hipEventElapsedTime(&t32, ev[1], ev[2]));
-        for (auto& e : ev) MPR_HIP(hipEventDestroy(e));
-        variant = t16 < t32 ? 0 : 1;
-        done = 2;
-        if (variant == 0) {                // the work list after sweep 2 was built for tiles of height 32
-            MPR_HIP(hipMemcpyAsync(&runs[0], w.runs, sizeof(mpr::BatchRun) * n_scenes, hipMemcpyDeviceToHost, s));
-            MPR_HIP(hipStreamSynchronize(s));
-            int64_t acc = 0;
-            for (int i = 0; i < n_scenes; ++i) {
-                prefix[i] = acc;
-                if (runs[order[i]].phase < 2) acc += work16[order[i]];
-            }
-            prefix[n_scenes] = acc;
-            MPR_HIP(hipMemcpyAsync(w.prefix, prefix.data(), sizeof(int64_t) * (n_scenes + 1), hipMemcpyHostToDevice,
-                                   s));
-            MPR_HIP(hipStreamSynchronize(s));
-        }
-    }
-    if (tile_h_used_out) *tile_h_used_out = variant ? 32 : 16;
-
-    // ---- the sweep loop: a graph of n_f sweeps replayed until every scene is done ----
-    const int per_graph = c.stop_mode == MPR_STOP_AUTO ? std::max(1, c.n_f) : 5;
-    hipGraphExec_t exec = nullptr;
-    hipStream_t cs = capture_stream();
-    if (cs) {
-        hipGraph_t graph = nullptr;
-        bool okc = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) == hipSuccess;
-        for (int i = 0; okc && i < per_graph; ++i)
-            okc = mpr::launch_batch_step(b, variant, variant, grid, max_hw_blocks, cs) == hipSuccess;
-        hipError_t ec = hipStreamEndCapture(cs, &graph);
-        if (okc && ec == hipSuccess && graph) {
-            if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) exec = nullptr;
-        }
-        if (graph) (void)hipGraphDestroy(graph);
-    }
-    int active = n_scenes;
-    while (active > 0 && done < total_max + 1) {
-        if (exec) {
-            MPR_HIP(hipGraphLaunch(exec, s));
-        } else {
-            for (int i = 0; i < per_graph; ++i) MPR_HIP(mpr::launch_batch_step(b, variant, variant, grid, max_hw_blocks, s));
-        }
-        done += per_graph;
-        mpr::BatchCtl hc;
-        MPR_HIP(hipMemcpyAsync(&hc, w.ctl, sizeof hc, hipMemcpyDeviceToHost, s));
-        MPR_HIP(hipStreamSynchronize(s));
-        active = hc.n_active;
-    }
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (active > 0) return fail(MPR_ERR_HIP, "batched simulation did not finish within %d sweeps", total_max);
-
-    // ---- results: final buffers into the callers' state, k* per scene ----
-    MPR_HIP(hipMemcpyAsync(runs.data(), w.runs, sizeof(mpr::BatchRun) * n_scenes, hipMemcpyDeviceToHost, s));
-    MPR_HIP(hipStreamSynchronize(s));
+    std::vector<double> rows, window((size_t)std::max(1, c.n_fit));
     bool all_converged = true;
-    for (int i = 0; i < n_scenes; ++i) {
-        const int total = runs[i].k_star + c.n_samp;
-        if (total & 1)
-            MPR_HIP(hipMemcpyAsync(scenes[i].state, w.alt[i], sizeof(float) * (size_t)(R * hs[i].HW),
-                                   hipMemcpyDeviceToDevice, s));
-        if (sweeps_done_out) sweeps_done_out[i] = runs[i].k_star;
-        if (converged_out) converged_out[i] = runs[i].converged != 0 ? 1 : 0;
-        all_converged &= runs[i].converged != 0;
+    int parity = 0;
+    for (int32_t k = 0; !active.empty();) {
+        const int32_t to = k + sweeps_to_check(c, k, cap - k);
+        while (k < to) {
+            b.parity = parity;
+            b.sweep = (uint32_t)(k + 1);
+            b.ns = std::min<int32_t>(depth, to - k);
+            MPR_HIP(mpr::launch_tile_batch(b, total, need_energy, s));
+            if (need_energy) MPR_HIP(mpr::launch_tile_batch_energy(b, w.means, n_scenes, w.ring, s));
+            parity ^= 1;
+            k += b.ns;
+        }
+        finished.clear();
+        rest.clear();
+        if (c.stop_mode == MPR_STOP_AUTO && k >= c.n_fit + c.n_f && (k - c.n_fit) % c.n_f == 0) {
+            rows.resize((size_t)(w.ring + 1) * n_scenes);
+            MPR_HIP(hipMemcpyAsync(rows.data(), w.means, sizeof(double) * rows.size(), hipMemcpyDeviceToHost, s));
+            MPR_HIP(hipStreamSynchronize(s));
+        } else if (c.stop_mode == MPR_STOP_AUTO) {
+            rows.clear();
+        }
+        for (int i : active) {
+            bool done = c.stop_mode != MPR_STOP_AUTO;
+            if (!done && !rows.empty()) {
+                for (int j = 0; j < c.n_fit; ++j)
+                    window[(size_t)j] = rows[(size_t)(1 + (k - c.n_fit + j) % w.ring) * n_scenes + i];
+                done = equilibrium_reached(rows[(size_t)i], window.data(), c.n_fit);
+            }
+            if (done || k >= cap) {
+                finished.push_back(i);
+                if (sweeps_done_out) sweeps_done_out[i] = k;
+                if (converged_out) converged_out[i] = done ? 1 : 0;
+                all_converged &= done;
+            } else {
+                rest.push_back(i);
+            }
+        }
+        if (finished.empty()) continue;
+        // the sampling sweeps of the scenes that have finished, then their states into the callers' buffers
+        MPR_HIP(upload(finished));
+        int p = parity;
+        for (int32_t si = 1; si <= c.n_samp; ++si) {
+            b.parity = p;
+            b.sweep = (uint32_t)(k + si);
+            b.ns = 1;
+            MPR_HIP(mpr::launch_tile_batch(b, total, false, s));
+            MPR_HIP(mpr::launch_tile_batch_accumulate(b, si == 1, max_blocks, s));
+            p ^= 1;
+        }
+        if (p)
+            for (int i : finished)
+                MPR_HIP(hipMemcpyAsync(scenes[i].state, w.alt[i], sizeof(float) * (size_t)(R * hs[i].a[0].HW),
+                                       hipMemcpyDeviceToDevice, s));
+        active.swap(rest);
+        MPR_HIP(upload(active));
     }
     if (!all_converged) return fail(MPR_WARN_NOT_CONVERGED, "some scenes reached n_max without equilibrium");
     return ok();
@@ -1695,8 +1627,8 @@ static mpr_status batched_tiles(const mpr_scene* scenes, int32_t n_scenes, const
 
 // The batch runs on the realization-lane sweep when the realizations fill a wave's lanes (64 or more; or when the
 // lane sweep is asked for), every side is below 65536 and all scenes find their temperatures the same way (one
-// persistent kernel instance serves them all); otherwise on the persistent tile-kernel batch.  Both give every
-// scene its single-scene results.
+// persistent kernel instance serves them all); otherwise on the tile sweeps.  Both give every scene its single-scene
+// results.
 static bool batch_on_lanes(const mpr_scene* scenes, int32_t n_scenes, const mpr_sim_config& c)
 {
     if (c.sweep_kernel == MPR_SWEEP_TILES) return false;

@@ -1,4 +1,4 @@
-// Device-side structures of the batched conditional simulation (batched.hip) and its launchers.
+// Device-side structures of the batch on the lane sweep (batched.hip) and its launchers (a batch below it: tiles.hpp).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -8,34 +8,11 @@
 
 namespace mpr {
 
-// One scene, as the batched kernels read it.  Geometry is kept for both tile heights (index 0: 16, 1: 32).
-struct BatchScene {
-    const float* t;
-    const uint8_t* mask;
-    const TBand* tp;
-    float* buf[2];        // state after an even / odd number of sweeps
-    double* acc;
-    long long* epart;     // [R][max tiles] energy partials (fixed point)
-    double* e_real;       // [R]
-    double* series;       // [cap + 1] realization-averaged energy per bond
-    int H, W, lb_h, lb_w, nbx, ntx, Mw;
-    int nty[2], ntiles[2], rchunk[2], nchunks[2];
-    int64_t HW;
-    uint32_t scene;
-    double inv_norm;      // 1 / (J * number of bonds)
-};
-
 struct BatchRun {
     int phase;            // 0 equilibrating, 1 sampling, 2 done
     int k_star;           // equilibration sweeps
     int samp;             // sampling sweeps accumulated
     int converged;        // 0 when the cap ended equilibration
-};
-
-struct BatchCtl {
-    int k;                        // sweeps done
-    int n_active;                 // scenes not done
-    unsigned long long queue;     // work-queue head of the current sweep
 };
 
 struct BatchCfg {
@@ -47,17 +24,6 @@ struct BatchCfg {
     int stop_mode, n_fit, n_f, n_max, n_eq, n_samp;
 };
 
-struct BatchDev {
-    BatchScene* scenes;
-    BatchRun* runs;
-    int* order;                   // scenes, largest work first
-    int64_t* prefix;              // [n + 1] work-list prefix over `order` (scenes still running)
-    BatchCtl* ctl;
-    BatchCfg cfg;
-    int n;
-};
-
-// ---- the batch on the realization-lane sweep (runs with 64 or more realizations) ----
 // One scene as the lane batch reads it: the arguments of its lane sweep (the sweep index is set per launch), its
 // window bits, temperature table, the two state buffers in the lane layout, and the per-scene reductions.
 struct BatchLaneScene {
@@ -106,9 +72,5 @@ hipError_t launch_batchl_step(const BatchLaneDev& b, int grid, int acc_blocks, h
 hipError_t launch_batchl_bounds(const BatchLaneDev& b, hipStream_t s);
 // *out += number of gap sites (mask 0) among mask[0 .. HW)
 hipError_t launch_count_gaps(const uint8_t* mask, int64_t HW, int64_t* out, hipStream_t s);
-
-hipError_t launch_batch_sweep(const BatchDev& b, int variant, int grid, hipStream_t s);
-hipError_t launch_batch_step(const BatchDev& b, int variant, int next_variant, int grid, int acc_blocks,
-                             hipStream_t s);
 
 }  // namespace mpr

@@ -86,20 +86,6 @@ struct InitArgs {
 };
 hipError_t launch_init(const InitArgs& a, hipStream_t s);
 
-struct SweepFusedArgs {
-    const float* src;    // [R][H][W] state after sweep k-1
-    float* dst;          // [R][H][W] state after sweep k (sample cells must already hold their angles)
-    const uint8_t* mask;
-    const TBand* Tb;
-    int H, W, lb_h, lb_w, nbx, ntx, nty, ntiles, Mw, R, rchunk, nchunks;
-    int tile_h;          // 16 or 32 (tile width is 64)
-    int64_t HW;
-    uint32_t sweep, real_offset, scene, key0, key1;
-    float q, J, delta_e;
-    double two_pi_q, Jd;
-    long long* e_partial;  // [R][ntiles] energy of each tile's colour-1 bonds (fixed point, 2^-32), or null
-};
-void fused_geometry(int64_t H, int64_t W, int R, int tile_h, int* ntx, int* nty, int* rchunk, int* nchunks);
 // Energies are accumulated in fixed point: each site's bond energy divided by J (at most 4 in magnitude) is
 // rounded to a multiple of 2^-24 (an int32), and the integers are summed exactly (int64 beyond a thread), so the
 // sums do not depend on their order.  kFixUnit converts back.

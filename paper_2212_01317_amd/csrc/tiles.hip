@@ -355,16 +355,19 @@ __device__ __forceinline__ int row_sum(int x)
     return x;
 }
 
-// ENERGY and SNAP are never both set: energies belong to the sweeps up to equilibrium, snapshots to the sampling ones.
+// The item of a workgroup.  XCD-aware order: workgroup g runs on XCD g % 8; consecutive items (adjacent tiles) go to the same
+// XCD.
+__device__ __forceinline__ uint32_t item_of(uint32_t nwork)
+{
+    return (blockIdx.x & 7u) * ((nwork + 7u) / 8u) + (blockIdx.x >> 3);
+}
+
+// Item `work` of a run: a tile and a chunk of its realizations.  ENERGY and SNAP are never both set: energies belong to the
+// sweeps up to equilibrium, snapshots to the sampling ones.
 template <bool TABLE, bool ENERGY, bool SNAP>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_sweeps(TileArgs a)
+__device__ __forceinline__ void tile_item(TileLds& L, TileArgs a, uint32_t work)
 {
     using C = Tl;
-    __shared__ TileLds L;
-    // XCD-aware order: workgroup g runs on XCD g % 8; consecutive items (adjacent tiles) go to the same XCD
-    const uint32_t nwork = (uint32_t)a.ntiles * (uint32_t)a.nchunks;
-    const uint32_t work = (blockIdx.x & 7u) * ((nwork + 7u) / 8u) + (blockIdx.x >> 3);
-    if (work >= nwork) return;
     const int tile = (int)(work % (uint32_t)a.ntiles);
     const int r0 = (int)(work / (uint32_t)a.ntiles) * a.rchunk;
     const int r1 = r0 + a.rchunk < a.R ? r0 + a.rchunk : a.R;
@@ -501,6 +504,88 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
+template <bool TABLE, bool ENERGY, bool SNAP>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_sweeps(TileArgs a)
+{
+    __shared__ TileLds L;
+    const uint32_t nwork = (uint32_t)a.ntiles * (uint32_t)a.nchunks, work = item_of(nwork);
+    if (work < nwork) tile_item<TABLE, ENERGY, SNAP>(L, a, work);
+}
+
+// A pointer read from memory, known to be global: flat accesses would wait for the LDS as well.
+template <class T>
+__device__ __forceinline__ T* in_global(T* p)
+{
+    return (T*)(__attribute__((address_space(1))) T*)(uint64_t)p;
+}
+
+// The scenes of a batch in one launch: items are numbered through the scenes of the list.  As in a single call up to five
+// sweeps stay in LDS, so that a launch, the staging and the pass over the states are paid once for them; a persistent queue
+// of (scene, tile, chunk) items with one sweep per launch and a graph of five launches a sweep took, for 60 sweeps at most,
+// 10.5 / 19.8 ms at 24 scenes of 64 .. 512 a side and R = 8 / 32 (4.7 / 11.8 so), 45.4 ms at 12 scenes of 256 .. 1024 and
+// R = 32 (27.5), 14.3 ms at 200 scenes of 16 .. 64 and R = 10 (11.4, of it most in the starts' small launches).  The scenes
+// still running advance in step, so a check reads all means in one copy.
+template <bool TABLE, bool ENERGY>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_batch(TileBatch b)
+{
+    __shared__ TileLds L;
+    const uint32_t nwork = b.prefix[b.n], work = item_of(nwork);
+    if (work >= nwork) return;
+    int lo = 0, hi = b.n;                     // prefix[lo] <= work < prefix[hi]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (b.prefix[mid] <= work) lo = mid;
+        else hi = mid;
+    }
+    // the scene's arguments through the constant address space: scalar loads
+    using CU = const __attribute__((address_space(4))) uint32_t;
+    const uint64_t ad = (uint64_t)(b.scenes[b.list[lo]].a + b.parity);
+    const CU* p = (const CU*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)ad) |
+                              (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(ad >> 32)) << 32);
+    static_assert(sizeof(TileArgs) % 4 == 0, "read in words");
+    uint32_t words[sizeof(TileArgs) / 4];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(TileArgs) / 4); ++i) words[i] = p[i];
+    TileArgs a;
+    __builtin_memcpy(&a, words, sizeof a);
+    a.src = in_global(a.src);
+    a.dst = in_global(a.dst);
+    a.mask = in_global(a.mask);
+    a.Tb = in_global(a.Tb);
+    a.plan = in_global(a.plan);
+    a.e_partial = in_global(a.e_partial);
+    a.sweep = b.sweep;
+    a.ns = b.ns;
+    tile_item<TABLE, ENERGY, false>(L, a, work - b.prefix[lo]);
+}
+
+// acc of the listed scenes += the gap angles of the state after the launch, over the realizations in order.
+__global__ __launch_bounds__(256) void k_tile_batch_accumulate(TileBatch b, int first)
+{
+    const TileScene& d = b.scenes[b.list[blockIdx.y]];
+    const float* const st = d.a[b.parity].dst;
+    const uint8_t* const mask = d.a[0].mask;
+    const int64_t HW = d.a[0].HW;
+    const int R = d.a[0].R;
+    for (int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x; n < HW; n += (int64_t)gridDim.x * 256) {
+        if (mask[n]) {
+            if (first) d.acc[n] = 0.0;
+            continue;
+        }
+        double v = first ? 0.0 : d.acc[n];
+        int r = 0;
+        for (; r + 8 <= R; r += 8) {          // eight loads in flight, added in order
+            float x[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = st[(int64_t)(r + k) * HW + n];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v += (double)x[k];
+        }
+        for (; r < R; ++r) v += (double)st[(int64_t)r * HW + n];
+        d.acc[n] = v;
+    }
+}
+
 // Sampling: one launch for the states of several sweeps (acc[n] is the sum over the states and, within a state, over the
 // realizations in order, as with one launch per sweep).  Launches and latency bound the small grids it is for: 128 x 128,
 // R = 10, 100 + 100 sweeps take 2.15 ms with a launch of both kernels per sampling sweep, 1.20 ms with one per five and
@@ -566,6 +651,27 @@ __device__ __forceinline__ void ordered_mean(const double* e_real, int R, double
 __global__ __launch_bounds__(64) void k_energy_mean_n(const double* e_real, int R, double* e_out, double* host)
 {
     ordered_mean(e_real + (int64_t)blockIdx.x * R, R, e_out + blockIdx.x, host ? host + blockIdx.x : nullptr);
+}
+
+// The energies of a launch of a batch: a workgroup per (scene of the list, sweep); sweep k's means also go to
+// means[1 + (k - 1) % ring][scene].
+__global__ __launch_bounds__(1024) void k_tile_batch_energy(TileBatch b, double* means, int n_scenes, int ring)
+{
+    const int lane = (int)(threadIdx.x & 63u), wv = (int)(threadIdx.x >> 6), scene = b.list[blockIdx.x];
+    const TileScene& d = b.scenes[scene];
+    const int R = d.a[0].R, nparts = d.a[0].ntiles;
+    double* const er = d.e_real + (int64_t)blockIdx.y * R;
+    for (int r = wv; r < R; r += 16) {
+        const long long* const row = d.a[0].e_partial + ((int64_t)blockIdx.y * R + r) * nparts;
+        long long s = 0;
+        for (int p = lane; p < nparts; p += 64) s += row[p];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) er[r] = ((double)s * kFixUnit) * d.inv_norm;
+    }
+    __syncthreads();
+    const int64_t k = (int64_t)b.sweep + blockIdx.y;
+    if (wv == 0) ordered_mean(er, R, d.series + k, means + (1 + (k - 1) % ring) * n_scenes + scene);
 }
 
 // Both steps in one workgroup per sweep, where the partials are few: one wave per realization at a time.
@@ -641,6 +747,45 @@ hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s)
     }
 #undef MPR_TILES
     return hipGetLastError();
+}
+
+bool tile_uses_table(const TileArgs& a) { return tile_table(a); }
+
+hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s)
+{
+    if (b.n <= 0 || work == 0) return hipSuccess;
+    const dim3 grid((work + 7u) / 8u * 8u);
+#define MPR_TILES(TAB, EN) hipLaunchKernelGGL((k_tile_batch<TAB, EN>), grid, dim3(kNT), 0, s, b)
+    if (b.table) {
+        if (energy) MPR_TILES(true, true);
+        else MPR_TILES(true, false);
+    } else {
+        if (energy) MPR_TILES(false, true);
+        else MPR_TILES(false, false);
+    }
+#undef MPR_TILES
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_batch_energy(const TileBatch& b, double* means, int n_scenes, int ring, hipStream_t s)
+{
+    if (b.n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_tile_batch_energy, dim3((unsigned)b.n, (unsigned)b.ns), dim3(1024), 0, s, b, means, n_scenes,
+                       ring);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_batch_accumulate(const TileBatch& b, bool first, int blocks, hipStream_t s)
+{
+    for (int at = 0; at < b.n; at += 65535) {              // (grid.y)
+        TileBatch part = b;
+        part.list = b.list + at;
+        const int n = b.n - at < 65535 ? b.n - at : 65535;
+        hipLaunchKernelGGL(k_tile_batch_accumulate, dim3((unsigned)blocks, (unsigned)n), dim3(256), 0, s, part, first ? 1 : 0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t HW, int R, int ns, bool first,

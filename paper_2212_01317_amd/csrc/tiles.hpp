@@ -37,6 +37,30 @@ struct TileArgs {
 hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s);
 // a.ns sweeps, src -> dst
 hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s);
+// One scene of a batch: the arguments of a launch from its first state buffer to the second, and back.
+struct TileScene {
+    TileArgs a[2];
+    double* e_real;            // [depth][R]
+    double* series;            // [cap + 1]
+    double* acc;
+    double inv_norm;
+};
+// A launch over the scenes list[0 .. n) (device arrays): items prefix[i] .. prefix[i + 1] are scene list[i]'s.
+struct TileBatch {
+    const TileScene* scenes;
+    const int* list;
+    const uint32_t* prefix;
+    int n, parity;             // a[parity]
+    uint32_t sweep;
+    int ns;
+    bool table;                // every scene's temperatures fit the LDS table
+};
+bool tile_uses_table(const TileArgs& a);
+hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s);
+// the energies of that launch into each scene's series, and the means of sweep k into means[1 + (k - 1) % ring][n_scenes]
+// (ring >= depth; row 0 is the starts')
+hipError_t launch_tile_batch_energy(const TileBatch& b, double* means, int n_scenes, int ring, hipStream_t s);
+hipError_t launch_tile_batch_accumulate(const TileBatch& b, bool first, int blocks, hipStream_t s);
 // acc[n] += the gap angles of ns states [ns][R][HW], state by state, over the realizations in order; first: from 0
 hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t HW, int R, int ns, bool first,
                                double* acc, hipStream_t s);
