@@ -140,21 +140,4 @@ __device__ __noinline__ bool exact64(float tp, float to, float nu, float nl, flo
     return dE <= 0.0;
 }
 
-// The exact directional decision, evaluated as the definition writes it: ah over the left and right neighbours, av
-// over the up and down neighbours (each term cos 2 pi q (t' - t_j) - cos 2 pi q (t - t_j), in the order up, left,
-// right, down), accept iff u2 < exp(J ah / Tx + J av / Ty).
-__device__ __noinline__ bool exact64_directional(float tp, float to, float nu, float nl, float nr, float nd,
-                                                 unsigned present, double two_pi_q, double J, float Tx, float Ty,
-                                                 float u2)
-{
-    double ah = 0.0, av = 0.0;
-    const double dtp = (double)tp, dto = (double)to;
-    if (present & 1u) av += cos(two_pi_q * (dtp - (double)nu)) - cos(two_pi_q * (dto - (double)nu));
-    if (present & 2u) ah += cos(two_pi_q * (dtp - (double)nl)) - cos(two_pi_q * (dto - (double)nl));
-    if (present & 4u) ah += cos(two_pi_q * (dtp - (double)nr)) - cos(two_pi_q * (dto - (double)nr));
-    if (present & 8u) av += cos(two_pi_q * (dtp - (double)nd)) - cos(two_pi_q * (dto - (double)nd));
-    const double w = J * ah / (double)Tx + J * av / (double)Ty;
-    return (double)u2 < exp(w);
-}
-
 }  // namespace mpr
