@@ -238,19 +238,18 @@ mpr_status mpr_validate(const float* zhat, const float* truth, const uint8_t* ev
 /* Batched simulation (a project addition): many scenes of different sizes and gap fractions, each with n_real
  * realizations.  Each scene follows exactly the arithmetic of mpr_simulate with cfg->scene_id replaced by its own
  * scene_id (its own stopping test and sampling sweeps), so its results are bit-identical to a single-scene call.
- * All scenes are advanced together by one persistent sweep kernel per sweep that takes work items from device work
- * queues, largest scenes first: with n_real >= 64 (cfg->sweep_kernel AUTO or LANES; or any n_real with LANES), the
- * realization-lane sweep over (scene, realization group, band, row segment) items from eight queues, one per XCD,
- * provided every scene's sides are below 65536 and all scenes share one temperature-lookup form (their lb_w all
- * multiples of the 12-column band, all at least 15 wide, or all otherwise); else (or with TILES) the tile sweep over
- * (scene, tile, realization chunk) items.  The sweeps, energies, stopping tests and sampling are replayed from a HIP
- * graph captured once per call (n_f sweeps per graph); the stream is synchronised once per graph replay.  On the
- * lane sweep the scenes' starts are spread over the caller's stream and three private streams of the library
- * (created once per host thread and device, default priority), forked from the caller's stream and joined back into
- * it by events, so that the call still begins after and ends before the caller's other work on `stream`.  The
- * per-chain stopping test (MPR_STOP_AUTO_CHAIN) is refused (MPR_ERR_INVALID_ARG).  tile_h: 16 or 32 (tile height of
- * the tile sweep; results do not depend on it), or 0 to time one sweep with each and keep the faster
- * (*tile_h_used_out reports the choice, 0 when the lane sweep ran).
+ * All scenes still running are advanced together.  With n_real >= 64 (cfg->sweep_kernel AUTO or LANES; or any n_real
+ * with LANES): by one persistent kernel per sweep, the realization-lane sweep over (scene, realization group, band, row
+ * segment) items from eight queues, one per XCD, largest scenes first, provided every scene's sides are below 65536 and
+ * all scenes share one temperature-lookup form (their lb_w all multiples of the 12-column band, all at least 15 wide, or
+ * all otherwise); sweeps, energies, stopping tests and sampling are replayed from a HIP graph captured once per call
+ * (n_f sweeps per graph), with the stream synchronised once per replay.  Else (or with TILES): by the tile sweep, up to
+ * five sweeps of all scenes per launch, with the stream synchronised at the checks and when the list of running scenes
+ * changes.  On the lane sweep the scenes' starts are spread over the caller's stream and three private streams of the
+ * library (created once per host thread and device, default priority), forked from the caller's stream and joined back
+ * into it by events, so that the call still begins after and ends before the caller's other work on `stream`.  The
+ * per-chain stopping test (MPR_STOP_AUTO_CHAIN) is refused (MPR_ERR_INVALID_ARG).  tile_h: 0, 16 or 32; results do not
+ * depend on it (*tile_h_used_out reports it, 32 for 0; 0 when the lane sweep ran).
  * sweeps_done_out[n_scenes] (host, optional): k* per scene; converged_out[n_scenes] (host, optional): 1 where the scene
  * met the equilibrium test (or ran FIXED), 0 where AUTO reached n_max without it (the call then returns
  * MPR_WARN_NOT_CONVERGED).  Workspace: mpr_simulate_batched_workspace_bytes (lane sweep: two lane buffers per
