@@ -559,6 +559,8 @@ __device__ __forceinline__ T* in_global(T* p)
     return (T*)(__attribute__((address_space(1))) T*)(uint64_t)p;
 }
 
+constexpr uint32_t kSlice = 1u << 22;   // items of a grid row: 2^31 threads
+
 // The scenes of a batch in one launch: items are numbered through the scenes of the list.  As in a single call up to five
 // sweeps stay in LDS, so that a launch, the staging and the pass over the states are paid once for them; a persistent queue
 // of (scene, tile, chunk) items with one sweep per launch and a graph of five launches a sweep took, for 60 sweeps at most,
@@ -569,8 +571,10 @@ template <bool TABLE, bool ENERGY>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_batch(TileBatch b)
 {
     __shared__ TileLds L;
-    const uint32_t nwork = b.prefix[b.n], work = item_of(nwork);
+    const uint32_t base = blockIdx.y * kSlice, rest = b.prefix[b.n] - base, nwork = rest < kSlice ? rest : kSlice;
+    uint32_t work = item_of(nwork);
     if (work >= nwork) return;
+    work += base;
     int lo = 0, hi = b.n;                     // prefix[lo] <= work < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -794,7 +798,7 @@ bool tile_uses_table(const TileArgs& a) { return tile_table(a); }
 hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s)
 {
     if (b.n <= 0 || work == 0) return hipSuccess;
-    const dim3 grid((work + 7u) / 8u * 8u);
+    const dim3 grid(work < kSlice ? (work + 7u) / 8u * 8u : kSlice, (work + kSlice - 1u) / kSlice);
 #define MPR_TILES(TAB, EN) hipLaunchKernelGGL((k_tile_batch<TAB, EN>), grid, dim3(kNT), 0, s, b)
     if (b.table) {
         if (energy) MPR_TILES(true, true);
