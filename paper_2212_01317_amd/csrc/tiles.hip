@@ -21,6 +21,7 @@
 // not loaded; a cell that is not loaded has (cos, sin) = (0, 0), which no angle has.
 #include <hip/hip_runtime.h>
 
+#include "items.hpp"
 #include "metropolis.hpp"
 #include "tiles.hpp"
 
@@ -395,13 +396,6 @@ __device__ __forceinline__ int row_sum(int x)
     return x;
 }
 
-// The item of a workgroup.  XCD-aware order: workgroup g runs on XCD g % 8; consecutive items (adjacent tiles) go to the same
-// XCD.
-__device__ __forceinline__ uint32_t item_of(uint32_t nwork)
-{
-    return (blockIdx.x & 7u) * ((nwork + 7u) / 8u) + (blockIdx.x >> 3);
-}
-
 // Item `work` of a run: a tile and a chunk of its realizations.  ENERGY and SNAP are never both set: energies belong to the
 // sweeps up to equilibrium, snapshots to the sampling ones.
 template <bool TABLE, bool ENERGY, bool SNAP>
@@ -548,8 +542,8 @@ template <bool TABLE, bool ENERGY, bool SNAP>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_sweeps(TileArgs a)
 {
     __shared__ TileLds L;
-    const uint32_t nwork = (uint32_t)a.ntiles * (uint32_t)a.nchunks, work = item_of(nwork);
-    if (work < nwork) tile_item<TABLE, ENERGY, SNAP>(L, a, work);
+    const uint32_t work = item_of(blockIdx.x, blockIdx.y, kItemRow, (uint32_t)a.ntiles * (uint32_t)a.nchunks);
+    if (work != kNoItem) tile_item<TABLE, ENERGY, SNAP>(L, a, work);
 }
 
 // A pointer read from memory, known to be global: flat accesses would wait for the LDS as well.
@@ -558,8 +552,6 @@ __device__ __forceinline__ T* in_global(T* p)
 {
     return (T*)(__attribute__((address_space(1))) T*)(uint64_t)p;
 }
-
-constexpr uint32_t kSlice = 1u << 22;   // items of a grid row: 2^31 threads
 
 // The scenes of a batch in one launch: items are numbered through the scenes of the list.  As in a single call up to five
 // sweeps stay in LDS, so that a launch, the staging and the pass over the states are paid once for them; a persistent queue
@@ -571,10 +563,8 @@ template <bool TABLE, bool ENERGY>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_batch(TileBatch b)
 {
     __shared__ TileLds L;
-    const uint32_t base = blockIdx.y * kSlice, rest = b.prefix[b.n] - base, nwork = rest < kSlice ? rest : kSlice;
-    uint32_t work = item_of(nwork);
-    if (work >= nwork) return;
-    work += base;
+    const uint32_t work = item_of(blockIdx.x, blockIdx.y, kItemRow, b.prefix[b.n]);
+    if (work == kNoItem) return;
     int lo = 0, hi = b.n;                     // prefix[lo] <= work < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -775,10 +765,18 @@ hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+namespace {
+
+dim3 item_grid(uint32_t nwork)
+{
+    return dim3(nwork < kItemRow ? (nwork + 7u) / 8u * 8u : kItemRow, (nwork + kItemRow - 1u) / kItemRow);
+}
+
+}  // namespace
+
 hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s)
 {
-    const int64_t nwork = (int64_t)a.ntiles * a.nchunks;
-    const dim3 grid((unsigned)((nwork + 7) / 8 * 8));
+    const dim3 grid = item_grid((uint32_t)a.ntiles * (uint32_t)a.nchunks);
 #define MPR_TILES(TAB, EN, SN) hipLaunchKernelGGL((k_tile_sweeps<TAB, EN, SN>), grid, dim3(kNT), 0, s, a)
     if (tile_table(a)) {
         if (a.e_partial) MPR_TILES(true, true, false);
@@ -798,7 +796,7 @@ bool tile_uses_table(const TileArgs& a) { return tile_table(a); }
 hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s)
 {
     if (b.n <= 0 || work == 0) return hipSuccess;
-    const dim3 grid(work < kSlice ? (work + 7u) / 8u * 8u : kSlice, (work + kSlice - 1u) / kSlice);
+    const dim3 grid = item_grid(work);
 #define MPR_TILES(TAB, EN) hipLaunchKernelGGL((k_tile_batch<TAB, EN>), grid, dim3(kNT), 0, s, b)
     if (b.table) {
         if (energy) MPR_TILES(true, true);
