@@ -233,7 +233,7 @@ size_t sim_ws(Carve& c, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const 
     const int nfull = mpr::energy_full_parts(H, W);
     const bool rl = use_rl(H, W, cfg), tiles = !rl && cfg->order != MPR_ORDER_DC;
     const mpr::RlGeom rg = mpr::rl_geometry(H, W, (int)R);
-    int64_t np = nfull;
+    int64_t np = rl ? mpr::lane_start_parts(cfg->init_mode, H * W) : nfull;
     const int ts = tile_sweeps_together(tg, R);
     if (tiles) np = std::max<int64_t>(np, (int64_t)tg.ntiles * ts);
     const int es = rl ? energy_sweeps((int64_t)rg.nbands * rg.nseg, R) : 1;
@@ -729,7 +729,7 @@ size_t batchl_ws(Carve& c, const mpr_scene* sc, int n, const mpr_sim_config* cfg
         x.cells.push_back(c.take<uint2>((H + 4) * (int64_t)g.nbands));
         x.buf0.push_back(c.take<float>((int64_t)g.Rp * H * W));
         x.buf1.push_back(c.take<float>((int64_t)g.Rp * H * W));
-        const int64_t np = std::max<int64_t>((int64_t)g.nbands * g.nseg, mpr::energy_full_parts(H, W));
+        const int64_t np = std::max<int64_t>((int64_t)g.nbands * g.nseg, mpr::lane_start_parts(cfg->init_mode, H * W));
         x.epart.push_back(c.take<long long>(np * R));
         x.e_real.push_back(c.take<double>(R));
         x.series.push_back(sc[i].energy ? sc[i].energy : c.take<double>((cap > 0 ? cap : 0) + 1));
@@ -1143,9 +1143,10 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
     if (need_energy) {
-        if (rl) MPR_HIP(mpr::launch_lane_start_energy(ia, w.rl[0], c.q, w.epart, nfull, s));
+        const int parts = rl ? mpr::lane_start_parts(c.init_mode, HW) : nfull;
+        if (rl) MPR_HIP(mpr::launch_lane_start_energy(ia, w.rl[0], c.q, w.epart, parts, s));
         else MPR_HIP(start_energy_partials(state, H, W, R, c, w.epart, nfull, s));
-        MPR_HIP(mpr::launch_energy_reduce_n(w.epart, nfull, R, 1, runner.inv_norm, w.e_real, w.series, host.at(0, 1), s));
+        MPR_HIP(mpr::launch_energy_reduce_n(w.epart, parts, R, 1, runner.inv_norm, w.e_real, w.series, host.at(0, 1), s));
     }
     // double checkerboard: in place in `state`, energy of the whole grid after the sweep
     mpr::DcArgs da;
@@ -1711,9 +1712,9 @@ static mpr_status batched_lanes(const mpr_scene* scenes, int32_t n_scenes, const
         const int64_t nbonds = sc.H * (sc.W - 1) + sc.W * (sc.H - 1);
         const double inv_norm = nbonds > 0 ? 1.0 / (double)nbonds : 0.0;
         if (energy) {
-            const int nfull = mpr::energy_full_parts(sc.H, sc.W);
-            MPR_HIP(mpr::launch_lane_start_energy(ia, w.buf0[i], c.q, w.epart[i], nfull, ss));
-            MPR_HIP(mpr::launch_energy_reduce(w.epart[i], nfull, R, inv_norm, w.e_real[i], w.series[i], ss));
+            const int parts = mpr::lane_start_parts(c.init_mode, HW);
+            MPR_HIP(mpr::launch_lane_start_energy(ia, w.buf0[i], c.q, w.epart[i], parts, ss));
+            MPR_HIP(mpr::launch_energy_reduce(w.epart[i], parts, R, inv_norm, w.e_real[i], w.series[i], ss));
         }
         if (c.n_samp == 0) MPR_HIP(hipMemsetAsync(sc.acc, 0, sizeof(double) * (size_t)HW, ss));
         MPR_HIP(mpr::launch_rl_cells(sc.mask, sc.H, sc.W, w.cells[i], ss));
@@ -2008,7 +2009,7 @@ size_t sim3_ws(Carve& c, int64_t D, int64_t H, int64_t W, int32_t lb_d, int32_t 
     x.lanes = c.take<float>((int64_t)g.Rp * g.n_all + 2 * mpr::kMargin3);
     if (x.lanes) x.lanes += mpr::kMargin3;
     const int es = energy_sweeps(g.nparts, R);
-    const int64_t np = std::max<int64_t>((int64_t)g.nparts * es, mpr::energy3_parts(D, H, W));
+    const int64_t np = std::max<int64_t>((int64_t)g.nparts * es, mpr::lane_start_parts(cfg->init_mode, g.n_all));
     x.epart = c.take<long long>(np * R);
     x.e_real = c.take<double>((int64_t)R * es);
     const int64_t cap = auto_stop(cfg->stop_mode) ? cfg->n_max : cfg->n_eq;
@@ -2177,9 +2178,9 @@ mpr_status mpr_simulate3d(const float* t, const uint8_t* mask, int64_t D, int64_
     const double inv_norm = nbonds > 0 ? 1.0 / (double)nbonds : 0.0;
     const bool need_energy = auto_stop(c.stop_mode) || energy_out != nullptr;
     if (need_energy) {
-        const int nfull = mpr::energy3_parts(D, H, W);
-        MPR_HIP(mpr::launch_lane_start_energy3(ia, w.lanes, c.q, w.epart, nfull, s));
-        MPR_HIP(mpr::launch_energy_reduce(w.epart, nfull, R, inv_norm, w.e_real, w.series, s));
+        const int parts = mpr::lane_start_parts(c.init_mode, g.n_all);
+        MPR_HIP(mpr::launch_lane_start_energy3(ia, w.lanes, c.q, w.epart, parts, s));
+        MPR_HIP(mpr::launch_energy_reduce(w.epart, parts, R, inv_norm, w.e_real, w.series, s));
     }
     MPR_HIP(mpr::launch_cells3(mask, D, H, W, g.nbands, w.cells, s));
 

@@ -751,13 +751,6 @@ hipError_t launch_block_stats3(const float* t, const uint8_t* mask, int64_t D, i
     return hipGetLastError();
 }
 
-int energy3_parts(int64_t D, int64_t H, int64_t W)
-{
-    const int64_t n = D * H * W;
-    const int64_t p = (n + 256 * 16 - 1) / (256 * 16);
-    return (int)(p < 1 ? 1 : (p > 256 ? 256 : p));
-}
-
 int lat3_zseg(int64_t D, int64_t H, int64_t W, int R)
 {
     const int64_t per = ((W + kB3 - 1) / kB3) * ((H + 1) / 2) * ((R + 63) / 64);

@@ -47,8 +47,6 @@ struct Init3Args {
     uint32_t real_offset, scene, key0, key1;
     int mode;
 };
-// parts of the energy of a start
-int energy3_parts(int64_t D, int64_t H, int64_t W);
 // gap bits of each row's window columns: [(D H) nbands]
 hipError_t launch_cells3(const uint8_t* mask, int64_t D, int64_t H, int64_t W, int nbands, uint32_t* cells,
                          hipStream_t s);

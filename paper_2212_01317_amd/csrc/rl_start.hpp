@@ -15,6 +15,8 @@ namespace mpr {
 // realizations r >= a.R get 0.  The buffers are aligned to 16 bytes.
 hipError_t launch_lane_start(const InitArgs& a, float* out0, float* out1, hipStream_t s);
 hipError_t launch_lane_start3(const Init3Args& a, float* out, hipStream_t s);
+// parts of the energy of a start (mode as in InitArgs) of N sites
+int lane_start_parts(int mode, int64_t N);
 // the energy partials of k_energy_full (the same per-site terms, so the same integer sums) of that start, partial[R][nparts]:
 // a block-mean start holds the same state in every realization, so realization 0's are formed and copied to the others
 hipError_t launch_lane_start_energy(const InitArgs& a, const float* lanes, float q, long long* partial, int nparts,
