@@ -841,7 +841,7 @@ hipError_t launch_accumulate_n(const float* states, const uint8_t* mask, int64_t
 hipError_t launch_energy_reduce_n(const long long* partial, int nparts, int R, int ns, double inv_norm, double* e_real,
                                   double* e_out, double* host, hipStream_t s)
 {
-    if ((int64_t)nparts * R <= 32768) {
+    if ((int64_t)((nparts + 63) / 64) * ((R + 15) / 16) <= 8) {        // (loads of a wave, one after another)
         hipLaunchKernelGGL(k_energy_small, dim3((unsigned)ns), dim3(1024), 0, s, partial, nparts, R, inv_norm, e_real,
                            e_out, host);
         return hipGetLastError();
