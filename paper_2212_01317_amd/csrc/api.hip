@@ -524,6 +524,7 @@ struct TileRunner {
     float* buf[2];
     int cur;
     double inv_norm;
+    bool planned = true;
     long long* epart;  // [depth][R][ntiles]
     double* e_real;    // [depth][R]
     hipStream_t s;
@@ -576,7 +577,19 @@ struct TileRunner {
     float* current() const { return buf[cur]; }
 
     // the update lists; the start must be in place (the samples' angles are read from it)
-    hipError_t plan() { return mpr::launch_tile_plan(a, s); }
+    hipError_t plan() { return planned ? mpr::launch_tile_plan(a, s) : hipSuccess; }
+
+    // For a run of n sweeps in all: the plan pays from the third sweep where the tile sweeps' 512 workgroup slots are not full
+    // (one realization each), from the fourth otherwise, and not where many realizations share each workgroup's staging, or
+    // rows of a tile are mostly empty (its ring is then most of the work).  Plan / a sweep per launch without one, in us with the
+    // calls around it: 4096^2, R = 1: one sweep 324 / 224, three 618 / 584, ten 978 / 1830; 256^2, R = 10: 37 / 30, 59 / 70,
+    // 86 / 211; 300 x 2000, R = 200: 1075 / 790, 2440 / 1720, 5390 / 4660; 1 x 5000, R = 200, ten: 1030 / 740.
+    void for_sweeps(int64_t n)
+    {
+        const int64_t items = (int64_t)a.ntiles * a.R;
+        const bool thin = a.H < 8;
+        planned = n > 3 ? items < (thin ? 8192 : 49152) : n > 1 && !thin && items < (n == 2 ? 512 : 640);
+    }
 
     // sweeps k .. k + n - 1, up to depth of them a launch; with e_dst set, their energies go to e_dst[0 .. n), n at most
     // tile_sweeps_together; with snap set (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
@@ -584,13 +597,14 @@ struct TileRunner {
     {
         hipError_t e = hipSuccess;
         for (int i = 0; i < n && e == hipSuccess; i += a.ns) {
-            a.ns = std::min(n - i, g.depth);
+            a.ns = planned ? std::min(n - i, g.depth) : 1;
             a.sweep = k + (uint32_t)i;
             a.snap = snap ? snap + (int64_t)i * a.R * a.HW : nullptr;
             a.src = buf[cur];
             a.dst = buf[cur ^ 1];
             a.e_partial = e_dst ? epart + (int64_t)i * a.R * a.ntiles : nullptr;
-            e = mpr::launch_tile_sweeps(a, s);
+            const bool one = a.ns == 1 && !snap && (!planned || (int64_t)a.ntiles * a.R >= 16384);
+            e = one ? mpr::launch_one_sweep(a, s) : mpr::launch_tile_sweeps(a, s);
             cur ^= 1;
         }
         if (e == hipSuccess && e_dst)
@@ -1140,6 +1154,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     HostSeries host;
     if (c.stop_mode == MPR_STOP_AUTO && !dc) host.open((int64_t)c.n_max + 1, s);
     TileRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.plan, w.epart, w.e_real, s);
+    runner.for_sweeps((int64_t)(auto_stop(c.stop_mode) ? c.n_max : c.n_eq) + c.n_samp);
     if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
     if (need_energy) {
@@ -1248,7 +1263,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     // chains have reached equilibrium: one launch, where the sweeps dropped at the end (below 0.1 ms at 2.4e7 sites) are
     // less than the checks cost (25 us each).  A whole 256 x 256 prediction that
     // stops by itself: 0.82 ms, 1.20 ms with a copy and a synchronisation at each check.
-    const int ahead_n = !host ? 0 : std::min<int64_t>(rl ? 1 : runner.g.depth, 24000000 / std::max<int64_t>(1, HW * R));
+    const int ahead_n = !host ? 0 : std::min<int64_t>(rl || !runner.planned ? 1 : runner.g.depth, 24000000 / std::max<int64_t>(1, HW * R));
     int32_t queued = 0;
     while (k < cap) {
         const int32_t to = k + sweeps_to_check(c, k, cap - k);
@@ -1298,7 +1313,8 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     if (c.n_samp == 0) {
         MPR_HIP(hipMemsetAsync(acc_out, 0, sizeof(double) * (size_t)HW, s));
     }
-    if (w.snap) {
+    const bool snaps = w.snap && runner.planned;
+    if (snaps) {
         const int per = snap_sweeps(H, W, R, c.n_samp, runner.g.depth);
         for (int32_t si = 0; si < c.n_samp; si += per) {
             const int n = std::min<int>(per, c.n_samp - si);
@@ -1306,7 +1322,7 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
             MPR_HIP(mpr::launch_accumulate_n(w.snap, mask, HW, R, n, si == 0, acc_out, s));
         }
     }
-    for (int32_t si = 1; si <= (w.snap ? 0 : c.n_samp); ++si) {
+    for (int32_t si = 1; si <= (snaps ? 0 : c.n_samp); ++si) {
         MPR_HIP(sweep((uint32_t)(k_star + si), 1, false));
         if (rl)             // with the last sum the state leaves the lanes too
             MPR_HIP(mpr::launch_lane_end(w.rl[rl_cur], mask, HW, R, si == 1 ? 1 : 0, si == c.n_samp ? state : nullptr,
@@ -1358,6 +1374,7 @@ mpr_status mpr_sweep(float* state, float* state_alt, const uint8_t* mask, int64_
     MPR_HIP(mpr::launch_tpairs(T_blocks, t_count(H, W, lb_h, lb_w, cfg), cfg->J, mpr::kDeltaE * cfg->J, w.tp, s));
     TileRunner runner(state, state_alt, mask, H, W, w.tp, t_lb(lb_h, *cfg), t_lb(lb_w, *cfg), *cfg, w.plan, w.epart,
                       w.e_real, s);
+    runner.for_sweeps(n_sweeps);
     if (n_sweeps > 0) MPR_HIP(runner.plan());
     // launches of odd numbers of sweeps, the last of one: the buffers end up as after one launch per sweep (the last
     // state in the one, the state before it in the other)

@@ -21,7 +21,6 @@
 // not loaded; a cell that is not loaded has (cos, sin) = (0, 0), which no angle has.
 #include <hip/hip_runtime.h>
 
-#include "items.hpp"
 #include "metropolis.hpp"
 #include "tiles.hpp"
 
@@ -764,15 +763,6 @@ hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s)
     else hipLaunchKernelGGL((k_tile_plan<false>), dim3((unsigned)a.ntiles), dim3(256), 0, s, a);
     return hipGetLastError();
 }
-
-namespace {
-
-dim3 item_grid(uint32_t nwork)
-{
-    return dim3(nwork < kItemRow ? (nwork + 7u) / 8u * 8u : kItemRow, (nwork + kItemRow - 1u) / kItemRow);
-}
-
-}  // namespace
 
 hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s)
 {

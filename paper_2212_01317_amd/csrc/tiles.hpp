@@ -4,6 +4,7 @@
 
 #include <cstdint>
 
+#include "items.hpp"
 #include "mpr_internal.hpp"
 
 namespace mpr {
@@ -33,10 +34,16 @@ struct TileArgs {
     float* snap;               // [ns][R][H][W]: the gap cells of every sweep's state too, or null (no energies then)
     long long* e_partial;      // [ns][R][ntiles] energy of each tile's colour-1 bonds (fixed point), or null
 };
+inline dim3 item_grid(uint32_t nwork)
+{
+    return dim3(nwork < kItemRow ? (nwork + 7u) / 8u * 8u : kItemRow, (nwork + kItemRow - 1u) / kItemRow);
+}
 // the plan of a call, from its mask and the sample angles of a.src (realization 0)
 hipError_t launch_tile_plan(const TileArgs& a, hipStream_t s);
 // a.ns sweeps, src -> dst
 hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s);
+// one sweep (a.ns == 1, no snapshots) without a plan, src -> dst, with its own chunks of realizations (onesweep.hip)
+hipError_t launch_one_sweep(const TileArgs& a, hipStream_t s);
 // One scene of a batch: the arguments of a launch from its first state buffer to the second, and back.
 struct TileScene {
     TileArgs a[2];
