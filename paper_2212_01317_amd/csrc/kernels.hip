@@ -1148,8 +1148,12 @@ __global__ __launch_bounds__(kSstNT) void k_sst_fused(const float* __restrict__ 
 hipError_t launch_sst(const float* T_blocks, int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, int32_t r_s,
                       int32_t n_s, double* a, double* b, float* out, hipStream_t s)
 {
-    if (n_s > 0 && (r_s == 1 || r_s == 2)) {      // wider windows: one pass per launch (their ring would outgrow the LDS)
-        const dim3 tiles((unsigned)(((W + kSstW - 1) / kSstW) * ((H + kSstH - 1) / kSstH)));
+    // fused: windows whose ring fits the LDS, on tiles three eighths full (radius 2: a quarter), or all in one round (two a CU).
+    // Emptier tiles cost the same each.  Five passes of radius 1, fused / a pass per launch: 1 x 2^20 sites 418 / 41 us,
+    // 3 x 300001 127 / 63, 100001 x 20 98 / 98 (radius 2: 146 / 182).
+    const int64_t ntiles = ((W + kSstW - 1) / kSstW) * ((H + kSstH - 1) / kSstH);
+    if (n_s > 0 && (r_s == 1 || r_s == 2) && (ntiles <= 512 || H * W * 8 >= (r_s == 1 ? 3 : 2) * ntiles * kSstW * kSstH)) {
+        const dim3 tiles((unsigned)ntiles);
         const double* in = nullptr;
         for (int32_t done = 0; done < n_s;) {
             const int p = n_s - done < kSstRing / r_s ? n_s - done : kSstRing / r_s;
