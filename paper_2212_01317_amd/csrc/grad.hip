@@ -244,6 +244,26 @@ __global__ __launch_bounds__(256) void k_grad_cov(const double* g, const double*
     dT[b] = T > 0.0 ? cov / (T * T) : 0.0;
 }
 
+// The same with a thread per block, whose loads are rows of H_rb: for many blocks.
+__global__ __launch_bounds__(256) void k_grad_cov_row(const double* g, const double* Hrb, int R, int64_t B,
+                                                       const float* T_blocks, double* dT)
+{
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (b >= B) return;
+    double gm = 0.0, hm = 0.0;
+    for (int r = 0; r < R; ++r) {
+        gm += g[r];
+        hm += Hrb[(int64_t)r * B + b];
+    }
+    gm /= (double)R;
+    hm /= (double)R;
+    double cov = 0.0;
+    for (int r = 0; r < R; ++r) cov += (g[r] - gm) * (Hrb[(int64_t)r * B + b] - hm);
+    cov /= (double)(R - 1);
+    const double T = (double)T_blocks[b];
+    dT[b] = T > 0.0 ? cov / (T * T) : 0.0;
+}
+
 int grad_parts(int64_t HW)
 {
     int64_t p = (HW + 256 * 16 - 1) / (256 * 16);
@@ -264,7 +284,12 @@ hipError_t launch_temperature_grad(const float* state, const double* Hrb, const 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_grad_g_final, dim3((unsigned)((R + 255) / 256)), dim3(256), 0, s, part, P, R, g);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_grad_cov, dim3((unsigned)((B + 7) / 8)), dim3(256), 0, s, g, Hrb, R, B, T_blocks, dT);
+    // a thread per block where the blocks alone fill the device, or nearly and the realizations are few: lanes / threads at
+    // 2^20 blocks, R = 8 150 / 25 us, at 2^18, R = 128 140 / 89, at 2^17, R = 16 29 / 18, R = 128 57 / 77, at 2^12, R = 512 20 / 126
+    if (B >= 196608 || (B >= 65536 && R <= 32))
+        hipLaunchKernelGGL(k_grad_cov_row, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, s, g, Hrb, R, B, T_blocks, dT);
+    else
+        hipLaunchKernelGGL(k_grad_cov, dim3((unsigned)((B + 7) / 8)), dim3(256), 0, s, g, Hrb, R, B, T_blocks, dT);
     return hipGetLastError();
 }
 
