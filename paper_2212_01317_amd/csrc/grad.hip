@@ -8,6 +8,7 @@
 // w_v = dL/dzhat_v * span at gaps.  Everything here is FP64 and reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -45,7 +46,7 @@ __device__ __forceinline__ double wave_sum8(const double* v, int lane)
 
 }  // namespace
 
-// One wave per chunk of a block's rows and RG realizations: partial H.  A bond inside the block is formed once, at its upper
+// One wave per chunk of a block's rows and RG = 8 realizations, or (RG = 1) a workgroup per chunk and realization: partial H.  A bond inside the block is formed once, at its upper
 // or left site, with weight 1 unless both ends are samples; a bond that leaves the block counts for the gap on this side, one
 // half where the other end is a gap too.  The weights of a site serve the RG realizations.  Bound by the FP64 cosines:
 // 512 x 512, 1024 realizations, 32 x 32 blocks: 0.81 ms, 3.20 ms when a workgroup per realization formed every bond from
@@ -56,8 +57,10 @@ __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ 
                                                        double* part /* [R][B * nchunk] */)
 {
     const int64_t wg = blockIdx.x;                // block * nchunk + chunk
-    const int lane = (int)(threadIdx.x & 63u);
-    const int r0 = ((int)blockIdx.y * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * RG;
+    const int lane = (int)(threadIdx.x & 63u), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    constexpr uint32_t step = RG == 1 ? 256 : 64;
+    const uint32_t me = RG == 1 ? threadIdx.x : (uint32_t)lane;
+    const int r0 = RG == 1 ? (int)blockIdx.y : ((int)blockIdx.y * 4 + wave) * RG;
     if (r0 >= R) return;
     const int b = (int)(wg / g.nchunk), c = (int)(wg % g.nchunk);
     const int by = b / g.nbx, bx = b % g.nbx;
@@ -69,7 +72,7 @@ __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ 
     for (int k = 0; k < RG; ++k) acc[k] = 0.0;
     if (y1 > y0) {
         const uint32_t cols = (uint32_t)(x1 - x0), sites = (uint32_t)(y1 - y0) * cols;
-        for (uint32_t i = lane; i < sites; i += 64) {
+        for (uint32_t i = me; i < sites; i += step) {
             const uint32_t row = i / cols;
             const int64_t y = y0 + row, x = x0 + (i - row * cols), n = y * g.W + x;
             const bool gap = !mask[n];
@@ -103,7 +106,7 @@ __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ 
         }
         // the gaps at the block's left and upper sides, whose bond to the next block starts there
         const uint32_t n_left = x0 > 0 ? (uint32_t)(y1 - y0) : 0u, n_up = c == 0 && yb > 0 ? cols : 0u;
-        for (uint32_t i = lane; i < n_left + n_up; i += 64) {
+        for (uint32_t i = me; i < n_left + n_up; i += step) {
             const int64_t n = i < n_left ? (y0 + i) * g.W + x0 : yb * g.W + x0 + (i - n_left);
             const int64_t other = i < n_left ? -1 : -g.W;
             if (mask[n]) continue;
@@ -122,10 +125,51 @@ __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ 
         k = lane >> 3;
         if (lane & 7) return;
     } else {
+        __shared__ double lds[4];
         sum = wave_sum64(acc[0]);
-        if (lane != 0) return;
+        if (lane == 0) lds[wave] = sum;
+        __syncthreads();
+        if (threadIdx.x != 0) return;
+        sum = ((lds[0] + lds[1]) + lds[2]) + lds[3];
     }
     if (r0 + k < R) part[(int64_t)(r0 + k) * gridDim.x + wg] = -J * sum;
+}
+
+// The same from the gap sites, each with its four bonds (one half of a bond to another gap), a workgroup per chunk and realization:
+// where the sites of a wave lie in different rows every load takes a cache line per lane, and the samples' are not made.
+__global__ __launch_bounds__(256) void k_block_energy_narrow(const float* __restrict__ state, const uint8_t* __restrict__ mask,
+                                                              StatsGeom g, double q, double J, int64_t HW,
+                                                              double* part /* [R][B * nchunk] */)
+{
+    __shared__ double lds[4];
+    const int64_t wg = blockIdx.x;
+    const int b = (int)(wg / g.nchunk), c = (int)(wg % g.nchunk);
+    const int by = b / g.nbx, bx = b % g.nbx;
+    const int64_t yb = (int64_t)by * g.lb_h, ye = yb + g.lb_h < g.H ? yb + g.lb_h : g.H;
+    const int64_t y0 = yb + (int64_t)c * g.G, y1 = y0 + g.G < ye ? y0 + g.G : ye;
+    const int64_t x0 = (int64_t)bx * g.lb_w, x1 = x0 + g.lb_w < g.W ? x0 + g.lb_w : g.W;
+    const float* s = state + (int64_t)blockIdx.y * HW;
+    double acc = 0.0;
+    if (y1 > y0) {
+        const uint32_t cols = (uint32_t)(x1 - x0), sites = (uint32_t)(y1 - y0) * cols;
+        for (uint32_t i = threadIdx.x; i < sites; i += 256) {
+            const uint32_t row = i / cols;
+            const int64_t y = y0 + row, x = x0 + (i - row * cols), n = y * g.W + x;
+            if (mask[n]) continue;
+            const double t = (double)s[n];
+            auto bond = [&](bool there, int64_t m) {
+                if (there) acc += (mask[m] ? 1.0 : 0.5) * cos_turns(q, t - (double)s[m]);
+            };
+            bond(y > 0, n - g.W);
+            bond(x > 0, n - 1);
+            bond(x + 1 < g.W, n + 1);
+            bond(y + 1 < g.H, n + g.W);
+        }
+    }
+    acc = wave_sum64(acc);
+    if ((threadIdx.x & 63u) == 0) lds[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + wg] = -J * (((lds[0] + lds[1]) + lds[2]) + lds[3]);
 }
 
 // The chunks of a block, added by P lanes (P a power of two), then across them.
@@ -145,12 +189,19 @@ hipError_t launch_block_energy(const float* state, const uint8_t* mask, const St
 {
     const int64_t nwg = g.B() * g.nchunk;
     const double q = (double)(float)(two_pi_q / (2.0 * kPi));        // (2 pi q, q an FP32 value)
-    // eight realizations per wave where that leaves four waves per SIMD
-    if (nwg * (R / 8) >= 4096)
+    // columns of one or two sites, tall enough that a wave's sites lie in rows of their own: 512 x 512, R = 512, 512 x 1
+    // blocks 5.28 / 2.91 ms, 512 x 2 2.40 / 2.19, 64 x 1 2.99 / 3.86, 512 x 4 1.16 / 1.33
+    const bool narrow = g.lb_w <= 2 && g.W >= 16 && std::min<int64_t>(g.lb_h, g.H) >= 128 * g.lb_w;
+    // eight realizations per wave where that leaves four waves per SIMD (fewer, and the rows of a few wide blocks, are a serial
+    // chain for a wave: 3 x 100000 in rows of its width, R = 8: 2.54 ms a wave each, 0.69 a workgroup each)
+    if (narrow)
+        hipLaunchKernelGGL(k_block_energy_narrow, dim3((unsigned)nwg, (unsigned)R), dim3(256), 0, s, state, mask, g, q, J,
+                           g.H * g.W, part);
+    else if (nwg * (R / 8) >= 4096)
         hipLaunchKernelGGL(k_block_energy<8>, dim3((unsigned)nwg, (unsigned)((R + 31) / 32)), dim3(256), 0, s, state, mask,
                            g, q, J, g.H * g.W, R, part);
     else
-        hipLaunchKernelGGL(k_block_energy<1>, dim3((unsigned)nwg, (unsigned)((R + 3) / 4)), dim3(256), 0, s, state, mask,
+        hipLaunchKernelGGL(k_block_energy<1>, dim3((unsigned)nwg, (unsigned)R), dim3(256), 0, s, state, mask,
                            g, q, J, g.H * g.W, R, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
