@@ -92,14 +92,14 @@ __device__ __forceinline__ bool here(float2 cs) { return cs.x != 0.0f || cs.y !=
 
 // ---- the plan: one workgroup per tile ----
 template <bool TABLE>
-__global__ __launch_bounds__(256) void k_tile_plan(TileArgs a)
+__device__ __forceinline__ void tile_plan(const TileArgs& a, int tile)
 {
     using C = Tl;
     __shared__ uint8_t kind[C::RH * C::RW];        // 0 not loaded, 1 gap, 2 sample
     __shared__ int cnt[4 * kD], pos[4 * kD];
     __shared__ int n_border;
     __shared__ long long esum[4];
-    const int tid = (int)threadIdx.x, tile = (int)blockIdx.x;
+    const int tid = (int)threadIdx.x;
     const TileBox b = tile_box(a, tile);
     uint32_t* const plan = a.plan + (size_t)tile * C::WORDS;
     for (int i = tid; i < C::RH * C::RW; i += 256) {
@@ -193,6 +193,12 @@ __global__ __launch_bounds__(256) void k_tile_plan(TileArgs a)
         plan[4 * kD + 1] = (uint32_t)e;
         plan[4 * kD + 2] = (uint32_t)(e >> 32);
     }
+}
+
+template <bool TABLE>
+__global__ __launch_bounds__(256) void k_tile_plan(TileArgs a)
+{
+    tile_plan<TABLE>(a, (int)blockIdx.x);
 }
 
 // ---- the sweeps ----
@@ -525,18 +531,9 @@ __device__ __forceinline__ T* in_global(T* p)
     return (T*)(__attribute__((address_space(1))) T*)(uint64_t)p;
 }
 
-// The scenes of a batch in one launch: items are numbered through the scenes of the list.  As in a single call up to five
-// sweeps stay in LDS, so that a launch, the staging and the pass over the states are paid once for them; a persistent queue
-// of (scene, tile, chunk) items with one sweep per launch and a graph of five launches a sweep took, for 60 sweeps at most,
-// 10.5 / 19.8 ms at 24 scenes of 64 .. 512 a side and R = 8 / 32 (4.7 / 11.8 so), 45.4 ms at 12 scenes of 256 .. 1024 and
-// R = 32 (27.5), 14.3 ms at 200 scenes of 16 .. 64 and R = 10 (11.4, of it most in the starts' small launches).  The scenes
-// still running advance in step, so a check reads all means in one copy.
-template <bool TABLE, bool ENERGY>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_batch(TileBatch b)
+// The arguments of the scene that item `work` of a batch belongs to; returns the scene's first item.
+__device__ __forceinline__ uint32_t batch_args(const TileBatch& b, uint32_t work, TileArgs* args)
 {
-    __shared__ TileLds L;
-    const uint32_t work = item_of(blockIdx.x, blockIdx.y, kItemRow, b.prefix[b.n]);
-    if (work == kNoItem) return;
     int lo = 0, hi = b.n;                     // prefix[lo] <= work < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
@@ -552,7 +549,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     uint32_t words[sizeof(TileArgs) / 4];
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(TileArgs) / 4); ++i) words[i] = p[i];
-    TileArgs a;
+    TileArgs& a = *args;
     __builtin_memcpy(&a, words, sizeof a);
     a.src = in_global(a.src);
     a.dst = in_global(a.dst);
@@ -560,9 +557,37 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     a.Tb = in_global(a.Tb);
     a.plan = in_global(a.plan);
     a.e_partial = in_global(a.e_partial);
+    return b.prefix[lo];
+}
+
+// The plans of all scenes in one launch: the items of a scene's first chunk of realizations.
+template <bool TABLE>
+__global__ __launch_bounds__(256) void k_tile_batch_plan(TileBatch b)
+{
+    const uint32_t work = item_of(blockIdx.x, blockIdx.y, kItemRow, b.prefix[b.n]);
+    if (work == kNoItem) return;
+    TileArgs a;
+    const uint32_t tile = work - batch_args(b, work, &a);
+    if (tile < (uint32_t)a.ntiles) tile_plan<TABLE>(a, (int)tile);
+}
+
+// The scenes of a batch in one launch: items are numbered through the scenes of the list.  As in a single call up to five
+// sweeps stay in LDS, so that a launch, the staging and the pass over the states are paid once for them; a persistent queue
+// of (scene, tile, chunk) items with one sweep per launch and a graph of five launches a sweep took, for 60 sweeps at most,
+// 10.5 / 19.8 ms at 24 scenes of 64 .. 512 a side and R = 8 / 32 (4.7 / 11.8 so), 45.4 ms at 12 scenes of 256 .. 1024 and
+// R = 32 (27.5), 14.3 ms at 200 scenes of 16 .. 64 and R = 10 (11.4, of it most in the starts' small launches).  The scenes
+// still running advance in step, so a check reads all means in one copy.
+template <bool TABLE, bool ENERGY>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_tile_batch(TileBatch b)
+{
+    __shared__ TileLds L;
+    const uint32_t work = item_of(blockIdx.x, blockIdx.y, kItemRow, b.prefix[b.n]);
+    if (work == kNoItem) return;
+    TileArgs a;
+    const uint32_t first = batch_args(b, work, &a);
     a.sweep = b.sweep;
     a.ns = b.ns;
-    tile_item<TABLE, ENERGY, false>(L, a, work - b.prefix[lo]);
+    tile_item<TABLE, ENERGY, false>(L, a, work - first);
 }
 
 // acc of the listed scenes += the gap angles of the state after the launch, over the realizations in order.
@@ -755,6 +780,14 @@ hipError_t launch_tile_sweeps(const TileArgs& a, hipStream_t s)
 }
 
 bool tile_uses_table(const TileArgs& a) { return tile_table(a); }
+
+hipError_t launch_tile_batch_plan(const TileBatch& b, uint32_t work, hipStream_t s)
+{
+    if (b.n <= 0 || work == 0) return hipSuccess;
+    if (b.table) hipLaunchKernelGGL(k_tile_batch_plan<true>, item_grid(work), dim3(256), 0, s, b);
+    else hipLaunchKernelGGL(k_tile_batch_plan<false>, item_grid(work), dim3(256), 0, s, b);
+    return hipGetLastError();
+}
 
 hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s)
 {

@@ -63,6 +63,8 @@ struct TileBatch {
     bool table;                // every scene's temperatures fit the LDS table
 };
 bool tile_uses_table(const TileArgs& a);
+// (`work`: the items of the list)
+hipError_t launch_tile_batch_plan(const TileBatch& b, uint32_t work, hipStream_t s);
 hipError_t launch_tile_batch(const TileBatch& b, uint32_t work, bool energy, hipStream_t s);
 // the energies of that launch into each scene's series, and the means of sweep k into means[1 + (k - 1) % ring][n_scenes]
 // (ring >= depth; row 0 is the starts')
