@@ -575,7 +575,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kWaves3, kWa
         w.t0 = tb + ((int64_t)bz * a.nby + w.y0 / a.lb_h) * a.nbx + bcol;
         w.t1 = has1 ? tb + ((int64_t)bz * a.nby + (w.y0 + 1) / a.lb_h) * a.nbx + bcol : w.t0;
         z = w.stretch(z);
+        // the notes are written by lane 0 and read by the wave, and written again after that
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         for (uint32_t i = 0; i < w.nq; ++i) w.settle(i, tb);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     if (ENERGY && lane < a.R)
         epart[(int64_t)lane * ((int64_t)a.nrows * a.nbands * a.nzseg) + ((int64_t)rows * a.nbands + band) * a.nzseg +
