@@ -17,8 +17,9 @@
 // sorted by the number of sweeps a site's ring distance still admits, so that sweep i of n takes a prefix of the list.
 //
 // LDS: per colour and row the cells of that colour are contiguous, so a pair's neighbourhood is five vector reads at
-// immediate offsets of one index.  A cell's angle is stored negated (sign bit set, -0 for 0) when it is a sample or is
-// not loaded; a cell that is not loaded has (cos, sin) = (0, 0), which no angle has.
+// immediate offsets of one index.  A cell that is not loaded (outside the grid, or beyond ring 2 ns) has (cos, sin) = (0, 0),
+// which no angle has.  A pair stands in the bucket of the site that is needed longer, so its other site is updated once more
+// than it is needed, from cells that may not be loaded; nothing that still matters reads it after that.
 #include <hip/hip_runtime.h>
 
 #include "exact_lane.hpp"
@@ -87,7 +88,6 @@ __device__ __forceinline__ int ring(int yrel, int xrel)
 }
 
 __device__ __forceinline__ int to_fix(float x) { return __float2int_rn(x * 16777216.0f); }
-__device__ __forceinline__ bool fixed_cell(float t) { return __float_as_uint(t) >> 31; }
 __device__ __forceinline__ bool here(float2 cs) { return cs.x != 0.0f || cs.y != 0.0f; }
 
 // ---- the plan: one workgroup per tile ----
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(256) void k_tile_plan(TileArgs a)
 struct alignas(16) TileLds {
     using C = Tl;
     float2 cs[2 * C::CELLS];               // (cos, sin) of 2 pi q t, colour 0 then colour 1
-    float t[2 * C::CELLS];                 // angles; negative (or -0): never updated
+    float t[2 * C::CELLS];                 // angles
     uint32_t list[2 * C::CAP];
     uint16_t border[C::ECAP];
     TBand tab[kTabCap];                    // temperatures of the blocks the region touches
@@ -250,7 +250,7 @@ __device__ __forceinline__ void settle(Trial& x, const float* t, const TileArgs&
     unsigned long long left = __ballot(open);
     if (left == 0) return;
     const unsigned pres = (here(u) ? 1u : 0u) | (here(l) ? 2u : 0u) | (here(rt) ? 4u : 0u) | (here(d) ? 8u : 0u);
-    const float own = t[i_own], tu = fabsf(t[i_u]), tl = fabsf(t[i_l]), tr = fabsf(t[i_r]), td = fabsf(t[i_d]);
+    const float own = t[i_own], tu = t[i_u], tl = t[i_l], tr = t[i_r], td = t[i_d];
     const float u2 = x.ui * 5.9604644775390625e-8f;
     if (__popcll(__ballot(1)) >= 8 && __popcll(left) <= 4) {
         do {
@@ -416,7 +416,7 @@ __device__ __forceinline__ void tile_item(TileLds& L, TileArgs a, uint32_t work)
     }
     for (int i = tid; i < 2 * C::CELLS; i += kNT) {
         L.cs[i] = make_float2(0.0f, 0.0f);
-        L.t[i] = -0.0f;
+        L.t[i] = 0.0f;
     }
     for (int c = 0; c < 2; ++c) {
         const int np = (int)plan[(2 * c) * kD + a.ns - 1], n1 = (int)plan[(2 * c + 1) * kD + a.ns - 1];
@@ -449,7 +449,7 @@ __device__ __forceinline__ void tile_item(TileLds& L, TileArgs a, uint32_t work)
         if (sample[k] != 0) {
             const int li = (int)(cell[k] & 0xffffu);
             const float ang = a.q * pre[k];
-            L.t[li] = -pre[k];
+            L.t[li] = pre[k];
             L.cs[li] = make_float2(cos_rev(ang), sin_rev(ang));
             cell[k] = 0u;
             off[k] = 0;
@@ -659,8 +659,8 @@ __global__ __launch_bounds__(256) void k_energy_real_n(const long long* __restri
     if (threadIdx.x == 0) e_real[row] = ((double)(((red[0] + red[1]) + red[2]) + red[3]) * kFixUnit) * inv_norm;
 }
 
-// mean over the realizations, added in order: 64 at a time from the lanes' registers (see k_global_mean)
-// (and to host memory, for a host that waits for the value)
+// mean over the realizations, added in order: 64 at a time, one load per lane and reads of fixed lanes, which do not depend on
+// the sum (and to host memory, for a host that waits for the value)
 __device__ __forceinline__ void ordered_mean(const double* e_real, int R, double* out, double* host)
 {
     const int lane = (int)(threadIdx.x & 63u);
