@@ -207,8 +207,8 @@ struct SimWs {
     int* No;
     float* gmean;
     mpr::TBand* tp;
-    long long* epart;   // [R][max(ntiles, nfull)]
-    double* e_real;     // [R]
+    long long* epart;   // [sweeps reduced together][R][parts of one], or the start's [R][parts]
+    double* e_real;     // [sweeps reduced together][R]
     double* series;     // [cap + 1]
     double* hist;       // per-chain stop: every realization's energy after each sweep, [cap + 1][R]
     float* alt;         // [R][H][W] second state buffer (tile sweeps)
@@ -525,14 +525,16 @@ struct TileRunner {
     int cur;
     double inv_norm;
     bool planned = true;
-    long long* epart;  // [depth][R][ntiles]
-    double* e_real;    // [depth][R]
+    int slots;         // sweeps whose energies a run() may reduce together
+    long long* epart;  // [slots][R][ntiles]
+    double* e_real;    // [slots][R]
     hipStream_t s;
 
     TileRunner(float* state, float* alt, const uint8_t* mask, int64_t H, int64_t W, const mpr::TBand* tp,
-               int32_t lb_h, int32_t lb_w, const mpr_sim_config& c, uint32_t* plan, long long* epart_,
+               int32_t lb_h, int32_t lb_w, const mpr_sim_config& c, uint32_t* plan, int slots_, long long* epart_,
                double* e_real_, hipStream_t s_)
     {
+        slots = slots_;
         g = mpr::tile_geometry(H, W, c.n_real);
         a.src = state;
         a.dst = alt;
@@ -592,9 +594,10 @@ struct TileRunner {
     }
 
     // sweeps k .. k + n - 1, up to depth of them a launch; with e_dst set, their energies go to e_dst[0 .. n), n at most
-    // tile_sweeps_together; with snap set (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
+    // slots; with snap set (and no e_dst), their states to snap[0 .. n); e_host: the energies in host memory too
     hipError_t run(uint32_t k, int n, double* e_dst, float* snap = nullptr, double* e_host = nullptr)
     {
+        if (e_dst && n > slots) return hipErrorInvalidValue;
         hipError_t e = hipSuccess;
         for (int i = 0; i < n && e == hipSuccess; i += a.ns) {
             a.ns = planned ? std::min(n - i, g.depth) : 1;
@@ -1153,7 +1156,8 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     const bool dc = c.order == MPR_ORDER_DC;
     HostSeries host;
     if (c.stop_mode == MPR_STOP_AUTO && !dc) host.open((int64_t)c.n_max + 1, s);
-    TileRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.plan, w.epart, w.e_real, s);
+    TileRunner runner(state, w.alt, mask, H, W, w.tp, t_lb(lb_h, c), t_lb(lb_w, c), c, w.plan,
+                      tile_sweeps_together(mpr::tile_geometry(H, W, R), R), w.epart, w.e_real, s);
     runner.for_sweeps((int64_t)(auto_stop(c.stop_mode) ? c.n_max : c.n_eq) + c.n_samp);
     if (!rl && !dc) MPR_HIP(runner.plan());
     const int nfull = mpr::energy_full_parts(H, W);
@@ -1372,8 +1376,8 @@ mpr_status mpr_sweep(float* state, float* state_alt, const uint8_t* mask, int64_
     SweepWs w;
     sweep_ws(cv, H, W, lb_h, lb_w, cfg, &w);
     MPR_HIP(mpr::launch_tpairs(T_blocks, t_count(H, W, lb_h, lb_w, cfg), cfg->J, mpr::kDeltaE * cfg->J, w.tp, s));
-    TileRunner runner(state, state_alt, mask, H, W, w.tp, t_lb(lb_h, *cfg), t_lb(lb_w, *cfg), *cfg, w.plan, w.epart,
-                      w.e_real, s);
+    TileRunner runner(state, state_alt, mask, H, W, w.tp, t_lb(lb_h, *cfg), t_lb(lb_w, *cfg), *cfg, w.plan,
+                      mpr::tile_geometry(H, W, cfg->n_real).depth, w.epart, w.e_real, s);
     runner.for_sweeps(n_sweeps);
     if (n_sweeps > 0) MPR_HIP(runner.plan());
     // launches of odd numbers of sweeps, the last of one: the buffers end up as after one launch per sweep (the last
@@ -1527,8 +1531,8 @@ static mpr_status batched_tiles(const mpr_scene* scenes, int32_t n_scenes, const
         ia.mode = c.init_mode;
         MPR_HIP(mpr::launch_init(ia, s));
         MPR_HIP(mpr::launch_tpairs(sc.T_blocks, g.B(), c.J, mpr::kDeltaE * c.J, w.tp[i], s));
-        TileRunner run(sc.state, w.alt[i], sc.mask, sc.H, sc.W, w.tp[i], sc.lb_h, sc.lb_w, c, w.plan[i], w.epart[i],
-                       w.e_real[i], s);
+        TileRunner run(sc.state, w.alt[i], sc.mask, sc.H, sc.W, w.tp[i], sc.lb_h, sc.lb_w, c, w.plan[i],
+                       mpr::tile_geometry(sc.H, sc.W, R).depth, w.epart[i], w.e_real[i], s);
         run.a.scene = sc.scene_id;
         run.a.src = sc.state;
         run.a.dst = w.alt[i];
