@@ -250,7 +250,8 @@ __device__ __forceinline__ void settle(Trial& x, const float* t, const TileArgs&
     unsigned long long left = __ballot(open);
     if (left == 0) return;
     const unsigned pres = (here(u) ? 1u : 0u) | (here(l) ? 2u : 0u) | (here(rt) ? 4u : 0u) | (here(d) ? 8u : 0u);
-    const float own = t[i_own], tu = t[i_u], tl = t[i_l], tr = t[i_r], td = t[i_d];
+    // (angles are not negative; without the fabsf the kernels take three more registers and are 1 % slower)
+    const float own = t[i_own], tu = fabsf(t[i_u]), tl = fabsf(t[i_l]), tr = fabsf(t[i_r]), td = fabsf(t[i_d]);
     const float u2 = x.ui * 5.9604644775390625e-8f;
     if (__popcll(__ballot(1)) >= 8 && __popcll(left) <= 4) {
         do {
