@@ -1,5 +1,5 @@
-"""Block energies in each form of the kernel (eight realizations a wave, a workgroup per realization, from the gaps of narrow
-blocks) and on both sides of the rules between them, against the oracle."""
+"""Block energies in each form of the kernel (eight realizations a wave, one a wave, a workgroup per realization, from the gaps
+of narrow blocks) and on both sides of the rules between them, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("H,W,R,lb", [
     (130, 17, 3, (128, 1)), (130, 17, 3, (127, 1)), (260, 16, 2, (256, 2)), (260, 16, 2, (255, 2)), (260, 15, 2, (256, 2)),
     (300, 21, 2, (300, 1)), (300, 1, 2, (300, 1)), (127, 40, 2, (500, 1)), (128, 40, 2, (500, 1)), (2, 5000, 3, (1, 5000)),
-    (5, 3000, 9, (5, 3000)), (64, 64, 33, (8, 8)), (200, 200, 77, (4, 4)), (200, 200, 61, (5, 3)), (1, 1, 1, (1, 1))])
+    (5, 3000, 9, (5, 3000)), (64, 64, 33, (8, 8)), (200, 200, 77, (4, 4)), (60, 70, 5, (16, 16)), (60, 70, 5, (16, 17)), (100, 100, 12, (3, 3)),
+    (80, 90, 4, (31, 33)), (80, 90, 4, (32, 32)), (512, 260, 400, (16, 32)), (200, 200, 61, (5, 3)), (1, 1, 1, (1, 1))])
 def test_block_energy(H, W, R, lb):
     rng = np.random.default_rng(H + W + R)
     m = (rng.random((H, W)) < 0.4).astype(np.uint8)
