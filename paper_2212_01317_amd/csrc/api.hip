@@ -1267,7 +1267,8 @@ mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t 
     // chains have reached equilibrium: one launch, where the sweeps dropped at the end (below 0.1 ms at 2.4e7 sites) are
     // less than the checks cost (25 us each).  A whole 256 x 256 prediction that
     // stops by itself: 0.82 ms, 1.20 ms with a copy and a synchronisation at each check.
-    const int ahead_n = !host ? 0 : std::min<int64_t>(rl || !runner.planned ? 1 : runner.g.depth, 24000000 / std::max<int64_t>(1, HW * R));
+    const int ahead_n = !host ? 0 : std::min<int64_t>(rl || !runner.planned ? 1 : runner.g.depth,
+                                                      24000000 / std::max<int64_t>(1, HW * R));
     int32_t queued = 0;
     while (k < cap) {
         const int32_t to = k + sweeps_to_check(c, k, cap - k);
@@ -1651,8 +1652,10 @@ static mpr_status batched_tiles(const mpr_scene* scenes, int32_t n_scenes, const
 // The batch runs on the realization-lane sweep when the realizations fill a wave's lanes (64 or more; or when the
 // lane sweep is asked for), every side is below 65536 and all scenes find their temperatures the same way (one
 // persistent kernel instance serves them all); otherwise on the tile sweeps.  Both give every scene its single-scene
-// results.  60 sweeps at most, tiles against lanes: 24 scenes of 64 .. 512 a side 11.8 / 23.1 ms at R = 32 and
-// 16.7 / 23.3 ms at R = 48, 12 scenes of 256 .. 1024 27.2 / 33.6 ms and 39.2 / 33.6 ms: the sides meet between 48 and 64.
+// results.  64 is where a wave's lanes are full, not where the two are equally fast, which depends on the scenes too.  Tiles /
+// lanes in ms, 60 sweeps at most: 48 scenes of 64 .. 1024 a side R = 32 51 / 57, 40 63 / 58, 64 98 / 58; 12 of 256 .. 1024
+// R = 40 33 / 37, 48 40 / 37, 64 53 / 37; 24 of 64 .. 512 R = 64 23 / 24, 80 28.4 / 27.5, 128 41 / 28; 200 of 16 .. 64 R = 64
+// 15 / 25, 128 23 / 28.
 static bool batch_on_lanes(const mpr_scene* scenes, int32_t n_scenes, const mpr_sim_config& c)
 {
     if (c.sweep_kernel == MPR_SWEEP_TILES) return false;

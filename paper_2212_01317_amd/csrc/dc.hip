@@ -89,8 +89,8 @@ __device__ __forceinline__ bool decide(const DcArgs& a, const TBand& tb, float t
     const float co = cos_rev(a.q * to), so = sin_rev(a.q * to);
     const float X = fmaf(cp - co, Cx, (sp - so) * Sy);
     int dec = filter32(X, ui, tb, a.J, a.delta_e);
-    // A wave full of updates mostly has one open decision or none: its cosines by eight lanes (256 x 256, R = 10, 20 sweeps at 95%
-    // gaps: 926 -> 851 us; 876 when half of a wave's lanes had no update and fewer waves waited for one)
+    // A wave full of updates mostly has one open decision or none: its cosines by eight lanes (256 x 256, R = 10, 20 sweeps
+    // at 95 % gaps: 926 -> 851 us; 876 when half of a wave's lanes had no update and fewer waves waited for one)
     unsigned long long left = __ballot(dec < 0);
     if (left == 0) return dec > 0;
     const float u2 = ui * 5.9604644775390625e-8f;

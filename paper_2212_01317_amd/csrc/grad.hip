@@ -46,11 +46,12 @@ __device__ __forceinline__ double wave_sum8(const double* v, int lane)
 
 }  // namespace
 
-// One wave per chunk of a block's rows and RG realizations, or (GROUP, RG = 1) a workgroup: partial H.  A bond inside the block is formed once, at its upper
-// or left site, with weight 1 unless both ends are samples; a bond that leaves the block counts for the gap on this side, one
-// half where the other end is a gap too.  The weights of a site serve the RG realizations.  Bound by the FP64 cosines:
-// 512 x 512, 1024 realizations, 32 x 32 blocks: 0.81 ms, 3.20 ms when a workgroup per realization formed every bond from
-// both ends (1.62 with the bonds of the left and upper sides in the same loop, where a few lanes hold up each wave).
+// One wave per chunk of a block's rows and RG realizations, or (GROUP, RG = 1) a workgroup: partial H.  A bond inside the block
+// is formed once, at its upper or left site, with weight 1 unless both ends are samples; a bond that leaves the block counts
+// for the gap on this side, one half where the other end is a gap too.  The weights of a site serve the RG realizations.
+// Bound by the FP64 cosines: 512 x 512, 1024 realizations, 32 x 32 blocks: 0.81 ms, 3.20 ms when a workgroup per realization
+// formed every bond from both ends (1.62 with the bonds of the left and upper sides in the same loop, where a few lanes hold
+// up each wave).
 template <int RG, bool GROUP>
 __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ state, const uint8_t* __restrict__ mask,
                                                        StatsGeom g, double q, double J, int64_t HW, int R,
@@ -139,8 +140,9 @@ __global__ __launch_bounds__(256) void k_block_energy(const float* __restrict__ 
     if (r0 + k < R) part[(int64_t)(r0 + k) * gridDim.x + wg] = -J * sum;
 }
 
-// The same from the gap sites, each with its four bonds (one half of a bond to another gap), a workgroup per chunk and realization:
-// where the sites of a wave lie in different rows every load takes a cache line per lane, and the samples' are not made.
+// The same from the gap sites, each with its four bonds (one half of a bond to another gap), a workgroup per chunk and
+// realization: where the sites of a wave lie in different rows every load takes a cache line per lane, and the samples' are
+// not made.
 __global__ __launch_bounds__(256) void k_block_energy_narrow(const float* __restrict__ state, const uint8_t* __restrict__ mask,
                                                               StatsGeom g, double q, double J, int64_t HW,
                                                               double* part /* [R][B * nchunk] */)
@@ -196,9 +198,10 @@ hipError_t launch_block_energy(const float* state, const uint8_t* mask, const St
     // columns of one or two sites, tall enough that a wave's sites lie in rows of their own: 512 x 512, R = 512, 512 x 1
     // blocks 5.28 / 2.91 ms, 512 x 2 2.40 / 2.19, 64 x 1 2.99 / 3.86, 512 x 4 1.16 / 1.33
     const bool narrow = g.lb_w <= 2 && g.W >= 16 && std::min<int64_t>(g.lb_h, g.H) >= 128 * g.lb_w;
-    // eight realizations per wave where that leaves four waves per SIMD; else one, a wave each for small chunks and a workgroup each
-    // for large ones, whose sites are a serial chain for a wave.  Wave / workgroup each: 1024 x 1024, R = 4, 4 x 4 blocks 172 / 407 us,
-    // 16 x 16 33 / 40, 32 x 32 36 / 30; 154 x 148, R = 60, 32 x 32 20 / 14; 3 x 100000, R = 8, 1 x 100000 2.54 / 0.69 ms
+    // eight realizations per wave where that leaves four waves per SIMD; else one, a wave each for small chunks and a
+    // workgroup each for large ones, whose sites are a serial chain for a wave.  Wave / workgroup each: 1024 x 1024, R = 4,
+    // 4 x 4 blocks 172 / 407 us, 16 x 16 33 / 40, 32 x 32 36 / 30; 154 x 148, R = 60, 32 x 32 20 / 14; 3 x 100000, R = 8,
+    // 1 x 100000 2.54 / 0.69 ms
     const int64_t sites = std::min<int64_t>({g.lb_h, g.H, g.G}) * std::min<int64_t>(g.lb_w, g.W);
     if (narrow)
         hipLaunchKernelGGL(k_block_energy_narrow, dim3((unsigned)nwg, (unsigned)R), dim3(256), 0, s, state, mask, g, q, J,
