@@ -16,7 +16,10 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  Work is enqueued on it; a call returns
  *     without waiting unless its comment says it synchronises the stream.
  *   - Nothing is allocated on the device by the library: scratch memory is the caller's `workspace`, whose size is
- *     given by the matching *_workspace_bytes query.  The workspace must stay valid until the enqueued work ends.
+ *     given by the matching *_workspace_bytes query for the same arguments (every field of cfg may count).  The
+ *     workspace must stay valid until the enqueued work ends.  On the host, mpr_simulate with MPR_STOP_AUTO takes a
+ *     32 KiB block of pinned memory that the device writes; up to eight such blocks, shared by all threads and
+ *     streams, are kept for the life of the process.
  *   - The return value is an mpr_status; nothing throws across the ABI.  On any non-OK status mpr_last_error()
  *     returns a message (thread-local).  Argument checks happen before any work is enqueued.  A device error is
  *     reported as MPR_ERR_HIP by the call that observes it.
@@ -192,8 +195,11 @@ mpr_status mpr_calibrate_directional(const float* t, const uint8_t* mask, int64_
  * The workspace holds a second state buffer of n_real*H*W floats (the sweep reads one buffer and writes the other).
  * Outputs: state[n_real*H*W] (float; in: ignored, out: final states), acc_out[H*W] (double), energy_out[k* + 1]
  * (double, optional NULL; size n_max + 1 for AUTO, n_eq + 1 for FIXED), *sweeps_done_out = k* (host, optional).
- * FIXED mode is asynchronous; AUTO and AUTO_CHAIN synchronise the stream at every check.  Workspace:
- * mpr_simulate_workspace_bytes.  Calls with the same arguments give bit-identical results. */
+ * FIXED mode is asynchronous.  AUTO_CHAIN synchronises the stream at every check.  AUTO waits at every check until the
+ * energies up to it have reached pinned host memory; sweeps queued behind them may still run, and are dropped, when
+ * the run stops.  In the double-checkerboard order, with n_max > 4095 or without pinned memory it copies the energies
+ * and synchronises the stream instead.  Workspace: mpr_simulate_workspace_bytes.  Calls with the same arguments give
+ * bit-identical results. */
 size_t mpr_simulate_workspace_bytes(int64_t H, int64_t W, int32_t lb_h, int32_t lb_w, const mpr_sim_config* cfg);
 mpr_status mpr_simulate(const float* t, const uint8_t* mask, int64_t H, int64_t W, const float* T_blocks,
                         int32_t lb_h, int32_t lb_w, const mpr_sim_config* cfg, float* state, double* acc_out,
